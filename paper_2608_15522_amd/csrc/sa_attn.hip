@@ -32,8 +32,8 @@
 // kept; the keys of a row block may be split into runs whose partial rows
 // token_combine_kernel merges.
 //
-// f32 path: a plain per-row online softmax with K/V tiles in LDS (used by the
-// small fp32 workloads; fp32 MFMA would not change its role).
+// f32 path: fp32 matrix products (v_mfma_f32_16x16x4_f32) from operands held
+// in registers, the keys of a 16-row block split over the workgroup's waves.
 #include <algorithm>
 
 #include "sa_device.h"
@@ -764,88 +764,270 @@ token_combine_kernel(const float* __restrict__ part, int n_split, int P, int Lq,
 }
 
 // ---- fp32 path ------------------------------------------------------------
-constexpr int kF32Keys = 32;
+// One workgroup of kF32Waves waves per 16 query rows; the waves take the
+// 16-key tiles of the row block's list in turn and merge their partial rows
+// through LDS at the end.  fp32 calls are small (a few heads, a few thousand
+// tokens), so the keys are split inside the workgroup and the rows are cut
+// into the smallest matrix tile: that is what fills the chip.  All products
+// run on the matrix cores in fp32 (v_mfma_f32_16x16x4_f32, 157 TFLOP/s):
+//   S^T = K Q^T   lane (n, gk) = (l % 16, l / 16) holds Q[n] and K[n] at the
+//                 channels 16i + 4gk + e, and the result leaves the lane with
+//                 query n and keys 4gk .. 4gk+3;
+//   O^T += V^T P^T with k slot gk of step r standing for key 4gk + r, which
+//                 makes P's registers the B operand as they are, and row i of
+//                 channel tile (dq, e) standing for channel 64dq + 4i + e, so
+//                 that one 16-byte load of V feeds four channel tiles.
+// Each wave copies its own K tiles through its own LDS buffers (RowTile16)
+// and loads V into registers, both one tile ahead, so the loop has no
+// barrier.  The row max is raised only when a score exceeds it by 2^8 (decided per wave), so the exchange of
+// the max between the four lanes of a query is rare.
+// At B1 H4 L4680 d128 (0.28 of the pairs kept) it takes 172 us, 83 TFLOP/s,
+// of which the full rows' 293 tiles a wave group are the longest chain; the
+// one-thread-per-row form before it took 16.4 ms, this one with K loaded
+// straight into the operand layout 192-264 us.
+constexpr int kF32Waves = 4;
+constexpr int kF32Rows = 16;  // query rows per workgroup
+constexpr int kF32Keys = 16;  // keys per tile
 
 // GATHER: as in the bf16 kernel, row j of pair (b,h) is token
-// rows[b*n_rows + j] and every key block is kept.
+// rows[b*n_rows + j] and every key is kept.
 template <int D, bool GATHER>
-__global__ void __launch_bounds__(128)
+__global__ void __launch_bounds__(64 * kF32Waves, 2)
 sparse_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                        const float* __restrict__ v, float* __restrict__ o,
                        float* __restrict__ lse,
                        const int32_t* __restrict__ kv_idx,
                        const int32_t* __restrict__ kv_cnt, int L, int n_b,
-                       int block, float scale, const int32_t* __restrict__ rows,
+                       int block, Log2Scale c, const int32_t* __restrict__ rows,
                        int n_rows, int H) {
-  __shared__ float Kt[kF32Keys][D + 1];
-  __shared__ float Vt[kF32Keys][D];
-  const int pair = blockIdx.y;
-  const int r = blockIdx.x;
-  const size_t row_base = static_cast<size_t>(pair) * n_b + r;
-  int cnt = n_b;
-  const int32_t* idx = nullptr;
+  constexpr int KI = D / 16;  // 16-byte chunks of a lane's K or Q row
+  constexpr int DQ = D / 64;  // 64-channel groups of O
+  using KTile = RowTile16<D>;
+  // the waves' K buffers; after the loop, their partial rows
+  constexpr int kPartBytes = kF32Waves * kF32Rows * (D + 4) * 4;
+  constexpr int kRingBytes = kF32Waves * 2 * KTile::kBytes;
+  static_assert(kPartBytes <= kRingBytes, "the partial rows reuse the K buffers");
+  __shared__ __attribute__((aligned(1024))) char ring[kRingBytes];
+  float(*part)[kF32Rows][D + 4] = reinterpret_cast<float(*)[kF32Rows][D + 4]>(ring);
+  __shared__ float part_m[kF32Waves][kF32Rows], part_l[kF32Waves][kF32Rows];
+  __shared__ uint16_t list[GATHER ? 1 : kMaxBlocks];
+  __shared__ int n_list;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, gk = lane >> 4;
+  const int pair = blockIdx.x;
+  const int tpb = GATHER ? 1 : block / kF32Keys;  // key tiles of a key block
+  int row0 = blockIdx.y * kF32Rows;
+
   if constexpr (!GATHER) {
-    cnt = kv_cnt[row_base];
-    cnt = cnt < 0 ? 0 : (cnt > n_b ? n_b : cnt);
-    idx = kv_idx + row_base * n_b;
-  }
-  const float* qh = q + static_cast<size_t>(pair) * L * D;
-  const float* kh = k + static_cast<size_t>(pair) * L * D;
-  const float* vh = v + static_cast<size_t>(pair) * L * D;
-  const int tid = threadIdx.x;
-  int qrow = r * block + tid;
-  bool active = tid < block && qrow < L;
-  if constexpr (GATHER) {
-    active = tid < block && qrow < n_rows;
-    qrow = active ? rows[static_cast<size_t>(pair / H) * n_rows + qrow] : -1;
-    active = active && qrow >= 0 && qrow < L;
-  }
-
-  float qv[D], acc[D];
-#pragma unroll
-  for (int e = 0; e < D; ++e) {
-    qv[e] = active ? qh[static_cast<size_t>(qrow) * D + e] : 0.f;
-    acc[e] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-
-  for (int i = 0; i < cnt; ++i) {
-    const int kb = GATHER ? i : idx[i];
-    if (kb < 0 || kb >= n_b) continue;
-    const int kend = min((kb + 1) * block, L);
-    for (int key0 = kb * block; key0 < kend; key0 += kF32Keys) {
-      const int nk = min(kF32Keys, kend - key0);
-      __syncthreads();
-      for (int e = tid; e < nk * D; e += blockDim.x) {
-        const int j = e / D, dd = e % D;
-        Kt[j][dd] = kh[static_cast<size_t>(key0 + j) * D + dd];
-        Vt[j][dd] = vh[static_cast<size_t>(key0 + j) * D + dd];
+    // Row tiles of full lists (protected query blocks) take n_b / k_keep
+    // times as long as the others and start first: workgroup y of a pair
+    // takes row tile y % per_block of the (y / per_block)-th block in the
+    // order full lists, then the rest (every wave finds it by ballots).
+    const int per_block = block / kF32Rows;
+    const int slot = blockIdx.y / per_block;
+    const int32_t* cnts = kv_cnt + static_cast<size_t>(pair) * n_b;
+    int nfull = 0;
+    for (int i0 = 0; i0 < n_b; i0 += 64)
+      nfull += __popcll(__ballot(i0 + lane < n_b && cnts[i0 + lane] >= n_b));
+    const bool want_full = slot < nfull;
+    int skip = want_full ? slot : slot - nfull, r = 0;
+    for (int i0 = 0; i0 < n_b; i0 += 64) {
+      const bool in = i0 + lane < n_b;
+      uint64_t m = __ballot(in && (cnts[min(i0 + lane, n_b - 1)] >= n_b) == want_full);
+      const int c64 = __popcll(m);
+      if (skip < c64) {
+        for (; skip > 0; --skip) m &= m - 1;
+        r = i0 + __ffsll(static_cast<unsigned long long>(m)) - 1;
+        break;
       }
-      __syncthreads();
-      if (active) {
-        for (int j = 0; j < nk; ++j) {
-          float s = 0.f;
-#pragma unroll
-          for (int e = 0; e < D; ++e) s = fmaf(qv[e], Kt[j][e], s);
-          s *= scale;
-          const float m_new = fmaxf(m, s);
-          const float alpha = expf(m - m_new);
-          const float p = expf(s - m_new);
-          l = l * alpha + p;
-#pragma unroll
-          for (int e = 0; e < D; ++e) acc[e] = fmaf(acc[e], alpha, p * Vt[j][e]);
-          m = m_new;
-        }
+      skip -= c64;
+    }
+    r = __builtin_amdgcn_readfirstlane(r);
+    row0 = r * block + (blockIdx.y % per_block) * kF32Rows;
+    if (row0 >= L) return;  // row tiles of the last block past the last token
+    // the list's valid entries (wave 0), in list order
+    if (tid < 64) {
+      const size_t row_base = static_cast<size_t>(pair) * n_b + r;
+      const int32_t* idx = kv_idx + row_base * n_b;
+      int cnt = kv_cnt[row_base];
+      cnt = cnt < 0 ? 0 : (cnt > n_b ? n_b : cnt);
+      int at = 0;
+      for (int i0 = 0; i0 < cnt; i0 += 64) {
+        const int kb = i0 + lane < cnt ? idx[i0 + lane] : -1;
+        const bool ok = kb >= 0 && kb < n_b;
+        const uint64_t m = __ballot(ok);
+        if (ok) list[at + __popcll(m & ((1ull << lane) - 1ull))] = static_cast<uint16_t>(kb);
+        at += __popcll(m);
       }
+      if (lane == 0) n_list = at;
     }
   }
-  if (active) {
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-    float* orow = o + (static_cast<size_t>(pair) * L + qrow) * D;
+  const float* kh = k + static_cast<size_t>(pair) * L * D;
+  const float* vh = v + static_cast<size_t>(pair) * L * D;
+  int qrow = row0 + n;
+  bool qvalid = qrow < L;
+  if constexpr (GATHER) {
+    qvalid = qrow < n_rows;
+    qrow = qvalid ? rows[static_cast<size_t>(pair / H) * n_rows + qrow] : -1;
+    qvalid = qrow >= 0 && qrow < L;
+  }
+  const float* qh = q + static_cast<size_t>(pair) * L * D;
+  f32x4 qf[KI];
 #pragma unroll
-    for (int e = 0; e < D; ++e) orow[e] = acc[e] * inv;
-    if (lse != nullptr)
-      lse[static_cast<size_t>(pair) * L + qrow] = l > 0.f ? m + logf(l) : -INFINITY;
+  for (int i = 0; i < KI; ++i)
+    qf[i] = qvalid ? ldg_f32x4(qh + static_cast<size_t>(qrow) * D + 16 * i + 4 * gk)
+                   : f32x4{0.f, 0.f, 0.f, 0.f};
+  __syncthreads();  // the list is visible
+  const int T = GATHER ? ceil_div(L, kF32Keys) : n_list * tpb;
+  // First key of tile t; tiles of the last block that start past L hold no
+  // key (their loads read row L-1, their probabilities are zero).
+  auto tile_key0 = [&](int t) {
+    if constexpr (GATHER) return t * kF32Keys;
+    const int b = t / tpb;
+    return __builtin_amdgcn_readfirstlane(static_cast<int>(list[b])) * block +
+           (t - b * tpb) * kF32Keys;
+  };
+  KTile kt;
+  kt.init(ring + wave * 2 * KTile::kBytes, lane);
+  struct Tile {
+    f32x4 v[4][DQ];
+    int key0;
+  };
+  auto load = [&](int t, int buf, Tile& x) {
+    x.key0 = tile_key0(t);
+    kt.copy(kh, x.key0, L, buf);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const float* vs = vh + static_cast<size_t>(min(x.key0 + 4 * gk + s, L - 1)) * D + 4 * n;
+#pragma unroll
+      for (int dq = 0; dq < DQ; ++dq) x.v[s][dq] = ldg_f32x4(vs + 64 * dq);
+    }
+  };
+  f32x4 acc[DQ][4];
+#pragma unroll
+  for (int dq = 0; dq < DQ; ++dq)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[dq][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, lsum = 0.f;
+  // One tile, its K in buffer buf: the loads of tile t + kF32Waves go out
+  // first and land under this tile's products.
+  auto step = [&](int t, int buf, Tile& x, Tile& nx) {
+    wait_dma();
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 kf[KI];
+    kt.read(buf, kf);
+    load(min(t + kF32Waves, T - 1), buf ^ 1, nx);
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < KI; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        s0 = mfma16x16x4_f32(kf[i][e], qf[i][e], s0);
+        s1 = mfma16x16x4_f32(kf[i][e + 1], qf[i][e + 1], s1);
+      }
+    float s[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = s0[e] + s1[e];
+    // rows past L repeat row L-1's logit (already in the max) or belong to a
+    // tile without keys, which only raises the reference
+    const float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])) * c.hi;
+    if (__any(mx > m + kRescaleSlack)) {
+      float m_new = fmaxf(m, mx);
+      m_new = fmaxf(m_new, __shfl_xor(m_new, 16, 64));
+      m_new = fmaxf(m_new, __shfl_xor(m_new, 32, 64));
+      const float alpha = m == m_new ? 1.f : fast_exp2(m - m_new);  // 0 the first time
+      m = m_new;
+      lsum *= alpha;
+#pragma unroll
+      for (int dq = 0; dq < DQ; ++dq)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[dq][e] *= alpha;
+    }
+    const float mref = m == -INFINITY ? 0.f : m;  // only -inf scores so far: they weigh 0
+    float p[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      p[e] = fast_exp2(fmaf(s[e], c.hi, fmaf(s[e], c.lo, -mref)));
+    if (x.key0 + kF32Keys > L) {  // rows past L weigh nothing, whatever row L-1 holds
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (x.key0 + 4 * gk + e >= L) {
+          p[e] = 0.f;
+#pragma unroll
+          for (int dq = 0; dq < DQ; ++dq) x.v[e][dq] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    lsum += (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int dq = 0; dq < DQ; ++dq)
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+          acc[dq][w] = mfma16x16x4_f32(x.v[e][dq][w], p[e], acc[dq][w]);
+  };
+  Tile ta, tb;
+  if (wave < T) {
+    load(wave, 0, ta);
+    int t = wave;
+    for (; t + kF32Waves < T; t += 2 * kF32Waves) {
+      step(t, 0, ta, tb);
+      step(t + kF32Waves, 1, tb, ta);
+    }
+    if (t < T) step(t, 0, ta, tb);
+  }
+  wait_dma();
+  __syncthreads();  // every wave is past its last K read and copy: `part` may be written
+  lsum += __shfl_xor(lsum, 16, 64);
+  lsum += __shfl_xor(lsum, 32, 64);
+  if (gk == 0) {
+    part_m[wave][n] = m;
+    part_l[wave][n] = lsum;
+  }
+  // acc[dq][e][s] is channel 64dq + 16gk + 4s + e of query n
+#pragma unroll
+  for (int dq = 0; dq < DQ; ++dq)
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      *reinterpret_cast<f32x4*>(&part[wave][n][64 * dq + 16 * gk + 4 * s]) =
+          f32x4{acc[dq][0][s], acc[dq][1][s], acc[dq][2][s], acc[dq][3][s]};
+  __syncthreads();
+  // Merge the waves' rows in wave order; 4 channels of a row per thread.
+  constexpr int TPR = D / 4;
+  for (int u = tid; u < kF32Rows * TPR; u += 64 * kF32Waves) {
+    const int j = u / TPR, d4 = (u % TPR) * 4;
+    int orow = row0 + j;
+    bool ok = orow < L;
+    if constexpr (GATHER) {
+      ok = orow < n_rows;
+      orow = ok ? rows[static_cast<size_t>(pair / H) * n_rows + orow] : -1;
+      ok = orow >= 0 && orow < L;
+    }
+    if (!ok) continue;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) M = fmaxf(M, part_m[w][j]);
+    float den = 0.f;
+    f32x4 num = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) {
+      const float pm = part_m[w][j];  // -inf: no key seen, the row is zero
+      const float f = pm == -INFINITY ? 0.f : exp2f(pm - M);
+      const f32x4 x = *reinterpret_cast<const f32x4*>(&part[w][j][d4]);
+      den = fmaf(f, part_l[w][j], den);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) num[e] = fmaf(f, x[e], num[e]);
+    }
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    const f32x4 val = {num[0] * inv, num[1] * inv, num[2] * inv, num[3] * inv};
+    *reinterpret_cast<f32x4*>(o + (static_cast<size_t>(pair) * L + orow) * D + d4) = val;
+    if (lse != nullptr && d4 == 0)
+      lse[static_cast<size_t>(pair) * L + orow] =
+          den > 0.f ? static_cast<float>(static_cast<double>(M) * 0.6931471805599453 +
+                                         static_cast<double>(logf(den)))
+                : -INFINITY;
   }
 }
 
@@ -898,13 +1080,15 @@ void launch_sparse_attention_f32(const float* q, const float* k,
                                  const int32_t* kv_idx, const int32_t* kv_cnt,
                                  char* /*ws*/, hipStream_t s) {
   const int n_b = ceil_div(L, block);
-  const dim3 grid(n_b, B * H);
+  const dim3 grid(B * H, n_b * (block / kF32Rows));
   if (d == 128)
-    hipLaunchKernelGGL((sparse_attn_f32_kernel<128, false>), grid, dim3(128), 0, s, q, k, v,
-                       o, lse, kv_idx, kv_cnt, L, n_b, block, scale, nullptr, 0, H);
+    hipLaunchKernelGGL((sparse_attn_f32_kernel<128, false>), grid, dim3(64 * kF32Waves), 0, s, q,
+                       k, v, o, lse, kv_idx, kv_cnt, L, n_b, block, log2_scale(scale), nullptr, 0,
+                       H);
   else
-    hipLaunchKernelGGL((sparse_attn_f32_kernel<64, false>), grid, dim3(128), 0, s, q, k, v,
-                       o, lse, kv_idx, kv_cnt, L, n_b, block, scale, nullptr, 0, H);
+    hipLaunchKernelGGL((sparse_attn_f32_kernel<64, false>), grid, dim3(64 * kF32Waves), 0, s, q,
+                       k, v, o, lse, kv_idx, kv_cnt, L, n_b, block, log2_scale(scale), nullptr, 0,
+                       H);
 }
 
 // Dense rows gathered from Q ([B,H,Lq,d]; rows[b*n_rows + j], or j when rows
@@ -962,15 +1146,15 @@ void launch_protected_token_attention_f32(const float* q, const float* k, const 
                                           float* o, float* lse, int B, int H, int L, int d,
                                           float scale, const int32_t* tok_idx, int k_tok,
                                           hipStream_t s) {
-  constexpr int kRowBlock = kTokRowBlock;
-  const int n_b = ceil_div(L, kRowBlock);
-  const dim3 grid(ceil_div(k_tok, kRowBlock), B * H);
+  const dim3 grid(B * H, ceil_div(k_tok, kF32Rows));
   if (d == 128)
-    hipLaunchKernelGGL((sparse_attn_f32_kernel<128, true>), grid, dim3(128), 0, s, q, k, v,
-                       o, lse, nullptr, nullptr, L, n_b, kRowBlock, scale, tok_idx, k_tok, H);
+    hipLaunchKernelGGL((sparse_attn_f32_kernel<128, true>), grid, dim3(64 * kF32Waves), 0, s, q,
+                       k, v, o, lse, nullptr, nullptr, L, 0, 0, log2_scale(scale), tok_idx, k_tok,
+                       H);
   else
-    hipLaunchKernelGGL((sparse_attn_f32_kernel<64, true>), grid, dim3(128), 0, s, q, k, v,
-                       o, lse, nullptr, nullptr, L, n_b, kRowBlock, scale, tok_idx, k_tok, H);
+    hipLaunchKernelGGL((sparse_attn_f32_kernel<64, true>), grid, dim3(64 * kF32Waves), 0, s, q,
+                       k, v, o, lse, nullptr, nullptr, L, 0, 0, log2_scale(scale), tok_idx, k_tok,
+                       H);
 }
 
 }  // namespace sa

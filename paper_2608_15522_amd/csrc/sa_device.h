@@ -38,6 +38,29 @@ __device__ __forceinline__ f32x16 mfma32x32x16(u32x4 a, u32x4 b, f32x16 c) {
       __builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// fp32 products and sums: v_mfma_f32_16x16x4_f32.  A[i][k] sits in lane
+// i + 16k, B[k][j] in lane j + 16k, and C/D[i][j] in lane j + 16(i / 4),
+// element i % 4.  It runs at 64 flop per cycle and SIMD, twice the rate of
+// scalar fp32 FMAs, with the same fp32 rounding of products and sums.
+__device__ __forceinline__ f32x4 mfma16x16x4_f32(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 ldg_f32x4(const float* p) {
+  return *reinterpret_cast<const f32x4*>(p);
+}
+
+// scale * log2(e) as an fp32 pair: s * hi + s * lo carries the product to
+// about 2^-48, so a score's error is that of its dot product.
+struct Log2Scale {
+  float hi, lo;
+};
+inline Log2Scale log2_scale(float scale) {
+  const double c = static_cast<double>(scale) * 1.4426950408889634;
+  const float hi = static_cast<float>(c);
+  return {hi, static_cast<float>(c - static_cast<double>(hi))};
+}
+
 __device__ __forceinline__ f32x16 zero16() {
   f32x16 z;
 #pragma unroll
@@ -109,6 +132,55 @@ __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 16, "vmcnt field");
   __builtin_amdgcn_s_waitcnt(0x0F70 | N);
 }
+
+// A wave's private LDS buffers for 16-row tiles of an fp32 [L][D] matrix that
+// feed v_mfma_f32_16x16x4_f32 as one operand: lane (n, gk) = (l % 16, l / 16)
+// needs 16 bytes at channel 16i + 4gk of row n.  Loaded straight from memory
+// that way, consecutive lanes lie in 16 different rows and the CU's L1 takes
+// them one by one (11-14 bytes per cycle measured, the bound of the kernels
+// then); copied row by row into LDS they come in at full width.  16-byte
+// slot s of row r sits at slot s ^ r, so that the 16 rows of an operand read
+// fall into different banks.  Only the wave itself reads a buffer, so its own
+// vmcnt wait orders the copy and no barrier is needed.
+template <int D>
+struct RowTile16 {
+  static constexpr int kBytes = 16 * D * 4;     // one tile
+  static constexpr int kCopies = kBytes / 1024;  // copy instructions per tile
+  const char* lds;          // the wave's two buffers
+  uint32_t lds_addr;        // their LDS byte address
+  int row[kCopies];         // tile row copied by this lane
+  uint32_t col[kCopies];    // byte offset of the lane's source slot in the row
+  int rd;                   // lane offset of the operand reads (XOR 64i)
+
+  __device__ __forceinline__ void init(char* wave_lds, int lane) {
+    lds = wave_lds;
+    lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_void_t*)wave_lds);
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) {
+      const int chunk = 64 * i + lane;
+      row[i] = chunk / (D / 4);
+      col[i] = 16u * static_cast<uint32_t>((chunk % (D / 4)) ^ row[i]);
+    }
+    const int n = lane & 15, gk = lane >> 4;
+    rd = n * D * 4 + 16 * (gk ^ n);
+  }
+  // Copy rows [row0, row0 + 16) of src into buffer b; rows past L repeat row
+  // L - 1.  row0 is wave-uniform.
+  __device__ __forceinline__ void copy(const float* src, int row0, int L, int b) const {
+    const int first = __builtin_amdgcn_readfirstlane(min(row0, L - 1));
+    const char* base = reinterpret_cast<const char*>(src + static_cast<size_t>(first) * D);
+    const int limit = L - 1 - first;
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i)
+      lds_dma16(base, static_cast<uint32_t>(min(row[i], limit) * (D * 4)) + col[i],
+                lds_addr + b * kBytes + i * 1024);
+  }
+  __device__ __forceinline__ void read(int b, f32x4 (&dst)[D / 16]) const {
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i)
+      dst[i] = *reinterpret_cast<const f32x4*>(lds + b * kBytes + (rd ^ (64 * i)));
+  }
+};
 
 __device__ __forceinline__ u32x4 ldg16(const void* p) {
   return *reinterpret_cast<const u32x4*>(p);
