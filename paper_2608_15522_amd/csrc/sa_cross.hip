@@ -28,7 +28,7 @@
 // lse_v.
 // All bf16 kernels share one key-stream engine (below).  No atomics: every
 // output element has one writer, so results are reproducible.
-// fp32 inputs use plain per-thread kernels with the same outputs.
+// fp32 inputs run the same two passes on fp32 matrix products (fp32 path below).
 #include "sa_device.h"
 #include "sa_internal.h"
 
@@ -799,57 +799,182 @@ __global__ void v2a_finalize_kernel(const float* __restrict__ part,
 }
 
 // ---- fp32 path --------------------------------------------------------------
-// Row log2-sum-exp of scale*Q K^T over all keys: one thread per query row.
+// Both passes form 16 x 16 score tiles with v_mfma_f32_16x16x4_f32 (one
+// operand held in registers, the other streamed through each wave's own LDS
+// buffers, RowTile16) and take both directions in one launch (grid (a.n_wg + v.n_wg, P): the first a.n_wg
+// workgroups of a pair serve a->v, the rest v->a),
+// because either alone leaves most of the chip idle at the sizes fp32 is used
+// at.  At B1 H4 L_v4680 L_a512 d128 the two take 66 and 85 us (92 and 95 us
+// with the streamed operand loaded straight into registers); the
+// one-thread-per-row kernels before them took 39 ms.
+constexpr int kF32XWaves = 4;
+constexpr int kF32XKeys = 64;  // keys per column-mass workgroup, 16 per wave
+
+// One direction's share of a launch.
+struct F32Dir {
+  const float* q;   // [P][Lq][D]
+  const float* k;   // [P][Lk][D]
+  float2* part;     // LSE pass: (max, sum) [P][nchunk][Lq], or NULL
+  float* lse2;      // [P][Lq] log2-sum-exp: written by the LSE pass when part
+                    // is NULL, read by the column-mass pass
+  float* out;       // column mass [P][nchunk][Lk]
+  int Lq, Lk;
+  int nt;           // 16-row query tiles (LSE) or 64-key tiles (column mass)
+  int nchunk;       // key chunks (LSE) or query chunks (column mass)
+  int chunk;        // keys or queries per chunk
+  int n_wg;         // nt * nchunk workgroups per pair
+};
+
 template <int D>
-__global__ void __launch_bounds__(128)
-row_lse2_f32_kernel(const float* __restrict__ qm, const float* __restrict__ km,
-                    float* __restrict__ lse2, int P, int Lq, int Lk, float c) {
-  const size_t t = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= static_cast<size_t>(P) * Lq) return;
-  const size_t pair = t / Lq;
-  const float* qr = qm + t * D;
-  const float* kh = km + pair * Lk * D;
-  float qv[D];
+__device__ __forceinline__ void load_row_f32(const float* base, int row, int L, int gk,
+                                             f32x4 (&dst)[D / 16]) {
+  const float* src = base + static_cast<size_t>(min(row, L - 1)) * D + 4 * gk;
 #pragma unroll
-  for (int e = 0; e < D; ++e) qv[e] = qr[e];
-  float m = -INFINITY, l = 0.f;
-  for (int i = 0; i < Lk; ++i) {
-    float s = 0.f;
-#pragma unroll
-    for (int e = 0; e < D; ++e) s = fmaf(qv[e], kh[static_cast<size_t>(i) * D + e], s);
-    s *= c;
-    const float m_new = fmaxf(m, s);
-    l = l * exp2f(m - m_new) + exp2f(s - m_new);
-    m = m_new;
-  }
-  lse2[t] = m + log2f(l);
+  for (int i = 0; i < D / 16; ++i) dst[i] = ldg_f32x4(src + 16 * i);
 }
 
-// Column mass: out[b][i] = sum_h sum_j 2^(c * q_j . k_i - lse2[b,h,j]) for
-// key i; one thread per (b, key).
+// A B^T of two 16-row operands: element e of lane (n, gk) is row 4gk + e of A
+// against row n of B.
 template <int D>
-__global__ void __launch_bounds__(128)
-colmass_f32_kernel(const float* __restrict__ qm, const float* __restrict__ km,
-                   const float* __restrict__ lse2, float* __restrict__ out, int B,
-                   int H, int Lq, int Lk, float c) {
-  const size_t t = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= static_cast<size_t>(B) * Lk) return;
-  const size_t b = t / Lk, i = t % Lk;
-  float acc = 0.f;
-  for (int h = 0; h < H; ++h) {
-    const size_t pair = b * H + h;
-    float kv[D];
+__device__ __forceinline__ f32x4 tile_f32(const f32x4 (&a)[D / 16], const f32x4 (&b)[D / 16]) {
+  f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < D; ++e) kv[e] = km[(pair * Lk + i) * D + e];
-    const float* qh = qm + pair * Lq * D;
-    for (int j = 0; j < Lq; ++j) {
-      float s = 0.f;
+  for (int i = 0; i < D / 16; ++i)
 #pragma unroll
-      for (int e = 0; e < D; ++e) s = fmaf(qh[static_cast<size_t>(j) * D + e], kv[e], s);
-      acc += exp2f(s * c - lse2[pair * Lq + j]);
+    for (int e = 0; e < 4; e += 2) {
+      s0 = mfma16x16x4_f32(a[i][e], b[i][e], s0);
+      s1 = mfma16x16x4_f32(a[i][e + 1], b[i][e + 1], s1);
+    }
+  return s0 + s1;
+}
+
+// Merge of two (max, sum) pairs; a pair without keys is (-inf, 0).
+__device__ __forceinline__ float2 merge_lse(float2 a, float2 b) {
+  const float m = fmaxf(a.x, b.x);
+  if (m == -INFINITY) return make_float2(m, a.y + b.y);
+  return make_float2(m, a.y * exp2f(a.x - m) + b.y * exp2f(b.x - m));
+}
+
+// Log2-sum-exp of scale * Q K^T over a chunk of keys: one workgroup per 16
+// query rows, its waves taking the chunk's 16-key tiles in turn (S^T = K Q^T,
+// so a lane keeps a running (max, sum) of query n over its own keys).
+template <int D>
+__global__ void __launch_bounds__(64 * kF32XWaves)
+row_lse2_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
+  __shared__ __attribute__((aligned(1024))) char ring[kF32XWaves * 2 * RowTile16<D>::kBytes];
+  __shared__ float2 red[kF32XWaves][16];
+  const bool second = static_cast<int>(blockIdx.x) >= a.n_wg;
+  const F32Dir& p = second ? v : a;
+  const int wg = static_cast<int>(blockIdx.x) - (second ? a.n_wg : 0);
+  const int qt = wg % p.nt, ch = wg / p.nt, pair = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = lane & 15, gk = lane >> 4;
+  const int Lq = p.Lq, Lk = p.Lk;
+  const int k0 = ch * p.chunk, k1 = min(k0 + p.chunk, Lk);
+  f32x4 qf[D / 16];
+  const float* kh = p.k + static_cast<size_t>(pair) * Lk * D;
+  float m = -INFINITY, l = 0.f;
+  constexpr int kStep = 16 * kF32XWaves;
+  RowTile16<D> tile;
+  tile.init(ring + wave * 2 * RowTile16<D>::kBytes, lane);
+  int buf = 0;
+  tile.copy(kh, k0 + 16 * wave, Lk, 0);
+  load_row_f32<D>(p.q + static_cast<size_t>(pair) * Lq * D, 16 * qt + n, Lq, gk, qf);
+  for (int key = k0 + 16 * wave; key < k1; key += kStep) {
+    wait_dma();
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 kf[D / 16];
+    tile.read(buf, kf);
+    buf ^= 1;
+    if (key + kStep < k1) tile.copy(kh, key + kStep, Lk, buf);
+    __builtin_amdgcn_sched_barrier(0);
+    const f32x4 s = tile_f32<D>(kf, qf);
+    const float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])) * c.hi;
+    if (__any(mx > m + 8.f)) {
+      const float m_new = fmaxf(m, mx);
+      l *= m == m_new ? 1.f : fast_exp2(m - m_new);
+      m = m_new;
+    }
+    const float mref = m == -INFINITY ? 0.f : m;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = fast_exp2(fmaf(s[e], c.hi, fmaf(s[e], c.lo, -mref)));
+      l += key + 4 * gk + e < k1 ? x : 0.f;
     }
   }
-  out[t] = acc;
+  wait_dma();  // a wave without tiles still has its first copy in flight
+  float2 ml = make_float2(m, l);
+#pragma unroll
+  for (int o = 16; o <= 32; o <<= 1)
+    ml = merge_lse(ml, make_float2(__shfl_xor(ml.x, o, 64), __shfl_xor(ml.y, o, 64)));
+  if (gk == 0) red[wave][n] = ml;
+  __syncthreads();
+  const int row = 16 * qt + static_cast<int>(threadIdx.x);
+  if (threadIdx.x < 16 && row < Lq) {
+    ml = red[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < kF32XWaves; ++w) ml = merge_lse(ml, red[w][threadIdx.x]);
+    if (p.part != nullptr)
+      p.part[(static_cast<size_t>(pair) * p.nchunk + ch) * Lq + row] = ml;
+    else
+      p.lse2[static_cast<size_t>(pair) * Lq + row] = ml.x + log2f(ml.y);
+  }
+}
+
+// Column mass over a chunk of queries: out[pair][chunk][key] = sum over the
+// chunk's queries of 2^(c * q . k - lse2[q]).  A wave holds 16 keys (S^T =
+// K Q^T: a lane sums its keys 4gk .. 4gk+3 over the queries n, n+16, ...) and
+// streams the chunk's 16-query tiles; the 16 lanes of a key are added at the
+// end.
+template <int D>
+__global__ void __launch_bounds__(64 * kF32XWaves)
+colmass_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
+  __shared__ __attribute__((aligned(1024))) char ring[kF32XWaves * 2 * RowTile16<D>::kBytes];
+  const bool second = static_cast<int>(blockIdx.x) >= a.n_wg;
+  const F32Dir& p = second ? v : a;
+  const int wg = static_cast<int>(blockIdx.x) - (second ? a.n_wg : 0);
+  const int kt = wg % p.nt, ch = wg / p.nt, pair = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = lane & 15, gk = lane >> 4;
+  const int Lq = p.Lq, Lk = p.Lk;
+  const int key0 = kt * kF32XKeys + 16 * wave;
+  if (key0 >= Lk) return;
+  const int q0 = ch * p.chunk, q1 = min(q0 + p.chunk, Lq);
+  f32x4 kf[D / 16];
+  const float* qh = p.q + static_cast<size_t>(pair) * Lq * D;
+  const float* lh = p.lse2 + static_cast<size_t>(pair) * Lq;
+  float sum[4] = {0.f, 0.f, 0.f, 0.f};
+  auto load_lse = [&](int q) { return q + n < q1 ? lh[q + n] : INFINITY; };  // +inf: adds 0
+  RowTile16<D> tile;
+  tile.init(ring + wave * 2 * RowTile16<D>::kBytes, lane);
+  int buf = 0;
+  tile.copy(qh, q0, Lq, 0);
+  float ln = load_lse(q0);
+  load_row_f32<D>(p.k + static_cast<size_t>(pair) * Lk * D, key0 + n, Lk, gk, kf);
+  for (int q = q0; q < q1; q += 16) {
+    wait_dma();
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 qf[D / 16];
+    tile.read(buf, qf);
+    buf ^= 1;
+    const float lr = ln;
+    if (q + 16 < q1) {
+      tile.copy(qh, q + 16, Lq, buf);
+      ln = load_lse(q + 16);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const f32x4 s = tile_f32<D>(kf, qf);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum[e] += fast_exp2(fmaf(s[e], c.hi, fmaf(s[e], c.lo, -lr)));
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) sum[e] += __shfl_xor(sum[e], o, 64);
+    const int key = key0 + 4 * gk + e;
+    if (n == 0 && key < Lk)
+      p.out[(static_cast<size_t>(pair) * p.nchunk + ch) * Lk + key] = sum[e];
+  }
 }
 
 // K2, with the block means of K^v written to kbar when it is not NULL.
@@ -959,31 +1084,51 @@ void cross_f32(const float* q_a, const float* k_v, const float* q_v,
                int block, float* sal_v_tok, float* sal_v_blk, float* sal_a_tok,
                int accumulate, char* ws, hipStream_t s) {
   const CrossWs lay = cross_ws_layout(B, H, L_v, L_a);
-  const float c = scale * kLog2e;
+  const Log2Scale c = log2_scale(scale);
   const int P = B * H;
+  float2* lse_part = reinterpret_cast<float2*>(ws + lay.lse_part);
   float* lse_a = reinterpret_cast<float*>(ws + lay.lse_a);
   float* colmass = reinterpret_cast<float*>(ws + lay.colmass);
-  const size_t na = static_cast<size_t>(P) * L_a;
-  hipLaunchKernelGGL(row_lse2_f32_kernel<D>, dim3((na + 127) / 128), dim3(128), 0, s,
-                     q_a, k_v, lse_a, P, L_a, L_v, c);
-  const size_t nv = static_cast<size_t>(B) * L_v;
-  hipLaunchKernelGGL(colmass_f32_kernel<D>, dim3((nv + 127) / 128), dim3(128), 0, s,
-                     q_a, k_v, lse_a, colmass, B, H, L_a, L_v, c);
+  float* lse_v = reinterpret_cast<float*>(ws + lay.lse_v);
+  float* v2a_part = reinterpret_cast<float*>(ws + lay.v2a_part);
+  float* v2a_head = reinterpret_cast<float*>(ws + lay.v2a_head);
+  // Log2-sum-exps: a->v in chunks of 1024 video keys (merged below), v->a
+  // over all audio keys at once.
+  const int nchunk = ceil_div(L_v, kLseChunk);
+  auto dir = [&](const float* q, const float* k, float2* part, float* lse2, float* out, int Lq,
+                 int Lk, int nt, int nch, int chunk) {
+    return F32Dir{q, k, part, lse2, out, Lq, Lk, nt, nch, chunk, nt * nch};
+  };
+  F32Dir a = dir(q_a, k_v, nchunk > 1 ? lse_part : nullptr, lse_a, nullptr, L_a, L_v,
+                 ceil_div(L_a, 16), nchunk, kLseChunk);
+  F32Dir v = dir(q_v, k_a, nullptr, lse_v, nullptr, L_v, L_a, ceil_div(L_v, 16), 1, L_a);
+  if (q_v == nullptr) v.n_wg = 0;
+  hipLaunchKernelGGL(row_lse2_f32_kernel<D>, dim3(a.n_wg + v.n_wg, P), dim3(64 * kF32XWaves), 0, s, a,
+                     v, c);
+  if (nchunk > 1) {
+    const size_t nlse = static_cast<size_t>(P) * L_a;
+    hipLaunchKernelGGL(lse_combine_kernel, dim3((nlse + 63) / 64), dim3(64), 0, s, lse_part, lse_a,
+                       P, L_a, nchunk);
+  }
+  // Column masses: a->v over all audio queries, v->a in chunks of 512 video
+  // queries.
+  const int nchunk3 = ceil_div(L_v, kV2aChunk);
+  a = dir(q_a, k_v, nullptr, lse_a, colmass, L_a, L_v, ceil_div(L_v, kF32XKeys), 1, L_a);
+  v = dir(q_v, k_a, nullptr, lse_v, v2a_part, L_v, L_a, ceil_div(L_a, kF32XKeys), nchunk3,
+          kV2aChunk);
+  if (q_v == nullptr) v.n_wg = 0;
+  hipLaunchKernelGGL(colmass_f32_kernel<D>, dim3(a.n_wg + v.n_wg, P), dim3(64 * kF32XWaves), 0, s, a,
+                     v, c);
   const int n_b = ceil_div(L_v, block);
   hipLaunchKernelGGL(a2v_finalize_kernel, dim3(n_b, B), dim3(block), 0, s, colmass,
-                     sal_v_tok, sal_v_blk, L_v, 1,
+                     sal_v_tok, sal_v_blk, L_v, H,
                      1.0f / (static_cast<float>(H) * static_cast<float>(L_a)), accumulate);
   if (q_v != nullptr) {
-    float* lse_v = reinterpret_cast<float*>(ws + lay.lse_v);
-    float* v2a = reinterpret_cast<float*>(ws + lay.v2a_part);
-    const size_t nvq = static_cast<size_t>(P) * L_v;
-    hipLaunchKernelGGL(row_lse2_f32_kernel<D>, dim3((nvq + 127) / 128), dim3(128), 0, s,
-                       q_v, k_a, lse_v, P, L_v, L_a, c);
-    const size_t nak = static_cast<size_t>(B) * L_a;
-    hipLaunchKernelGGL(colmass_f32_kernel<D>, dim3((nak + 127) / 128), dim3(128), 0, s,
-                       q_v, k_a, lse_v, v2a, B, H, L_v, L_a, c);
-    hipLaunchKernelGGL(v2a_finalize_kernel, dim3((nak + 255) / 256), dim3(256), 0, s,
-                       v2a, sal_a_tok, B, 1, L_a,
+    hipLaunchKernelGGL(v2a_chunk_sum_kernel, dim3(ceil_div(L_a, 64), P), dim3(256), 0, s,
+                       v2a_part, v2a_head, L_a, nchunk3);
+    const size_t na = static_cast<size_t>(B) * L_a;
+    hipLaunchKernelGGL(v2a_finalize_kernel, dim3((na + 255) / 256), dim3(256), 0, s,
+                       v2a_head, sal_a_tok, B, H, L_a,
                        1.0f / (static_cast<float>(H) * static_cast<float>(L_v)), accumulate);
   }
 }
