@@ -1,10 +1,9 @@
 // Protected selection and the protected block mask.
 //
-// K4 select_protected (Sec. 4.2, Eq. (8) at block granularity): per batch
-//    item one workgroup sorts the block saliencies in LDS with a bitonic
-//    network on 64-bit keys (value descending, index ascending) and takes
-//    the first k_prot.
-// K5 block_pool: per (b,h) and 8 consecutive blocks the mean of Q and of K
+// K4 select_protected (Sec. 4.2, Eq. (8) at block granularity): every block's
+//    rank in its batch item by counting the smaller 64-bit keys (value
+//    descending, index ascending); the first k_prot are protected.
+// K5 block_pool: per (b,h) and 1 to 8 consecutive blocks the mean of Q and of K
 //    over the valid tokens of each block, accumulated in fp64 (16-byte loads,
 //    fixed-order LDS reduction; the sums are exact, see block_pool_kernel),
 //    stored as [d][n_pad] (block index innermost).
@@ -25,28 +24,39 @@ namespace sa {
 namespace {
 
 // ---- K4 ---------------------------------------------------------------------
-__global__ void __launch_bounds__(1024)
+// Grid (ceil(n_b / kSelBlocks), B), 256 threads.  Every workgroup holds the
+// batch item's keys in LDS and ranks kSelBlocks of its blocks: kSelParts
+// threads per block each count the smaller keys in a quarter of the list, and
+// the rank (keys are distinct) places the block.  No barrier chain: 36 bitonic
+// steps of one 1024-thread workgroup took 7.4 us at n_b = 256, two batch
+// items of n_b = 141 took 14.
+constexpr int kSelParts = 8;
+constexpr int kSelBlocks = 256 / kSelParts;
+__global__ void __launch_bounds__(256)
 select_protected_kernel(const float* __restrict__ sal_blk, int n_b, int k_prot,
-                        int n_pad, int32_t* __restrict__ prot_idx,
-                        uint8_t* __restrict__ prot_flag) {
+                        int32_t* __restrict__ prot_idx, uint8_t* __restrict__ prot_flag) {
   __shared__ uint64_t keys[kMaxBlocks];
-  __shared__ uint8_t flag[kMaxBlocks];
-  const int b = blockIdx.x;
+  __shared__ int cnt[kSelParts][kSelBlocks];
+  const int b = blockIdx.y, tid = threadIdx.x;
   const float* s = sal_blk + static_cast<size_t>(b) * n_b;
-  for (int i = threadIdx.x; i < n_pad; i += blockDim.x) {
-    keys[i] = i < n_b ? desc_value_asc_index_key(s[i], static_cast<uint32_t>(i))
-                      : ~0ull;
-    if (i < n_b) flag[i] = 0;
-  }
-  bitonic_sort_lds(keys, n_pad);
-  for (int i = threadIdx.x; i < k_prot; i += blockDim.x) {
-    const uint32_t c = static_cast<uint32_t>(keys[i] & 0xffffffffu);
-    flag[c] = 1;
-    if (prot_idx != nullptr) prot_idx[static_cast<size_t>(b) * k_prot + i] = c;
-  }
+  for (int i = tid; i < n_b; i += 256)
+    keys[i] = desc_value_asc_index_key(s[i], static_cast<uint32_t>(i));
   __syncthreads();
-  for (int i = threadIdx.x; i < n_b; i += blockDim.x)
-    prot_flag[static_cast<size_t>(b) * n_b + i] = flag[i];
+  const int t = tid % kSelBlocks, part = tid / kSelBlocks;
+  const int c = blockIdx.x * kSelBlocks + t;
+  const uint64_t mine = keys[min(c, n_b - 1)];
+  const int j0 = n_b * part / kSelParts, j1 = n_b * (part + 1) / kSelParts;
+  int below = 0;
+#pragma unroll 8
+  for (int j = j0; j < j1; ++j) below += keys[j] < mine;
+  cnt[part][t] = below;
+  __syncthreads();
+  if (part != 0 || c >= n_b) return;
+#pragma unroll
+  for (int p = 1; p < kSelParts; ++p) below += cnt[p][t];
+  prot_flag[static_cast<size_t>(b) * n_b + c] = below < k_prot ? 1 : 0;
+  if (prot_idx != nullptr && below < k_prot)
+    prot_idx[static_cast<size_t>(b) * k_prot + below] = c;
 }
 
 // ---- K5 ---------------------------------------------------------------------
@@ -71,7 +81,7 @@ template <> struct Elem<float> {
 
 constexpr int kMaxPoolBlock = 128;  // largest supported block
 
-// Grid (ceil(n_b / kPoolBlocks), P), 256 threads.  out[pair][:][c] (layout
+// Grid (ceil(n_b / PB), P), 256 threads.  out[pair][:][c] (layout
 // [d][n_pad]) = mean of the rows of block c, in fp64: a sum of at most 128
 // values is exact in fp64 whenever their magnitudes lie within 2^44 (bf16
 // inputs, 8 significant bits) or 2^28 (fp32, 24 bits) of each other, so the
@@ -79,11 +89,9 @@ constexpr int kMaxPoolBlock = 128;  // largest supported block
 // rounded once.  Per block, thread
 // (rg, cc) loads 16-byte chunk cc of rows rg, rg + RG, ... of both matrices
 // and the RG partial sums of each element are added in a fixed order; the
-// means of the workgroup's blocks are written as runs of consecutive
+// means of the workgroup's PB blocks are written as runs of consecutive
 // columns.
-constexpr int kPoolBlocks = 8;  // blocks per block_pool workgroup
-
-template <typename T, int D>
+template <typename T, int D, int PB>
 __global__ void __launch_bounds__(256)
 block_pool_kernel(const T* __restrict__ q, const T* __restrict__ k,
                   double* __restrict__ qbar, double* __restrict__ kbar, int L,
@@ -93,10 +101,10 @@ block_pool_kernel(const T* __restrict__ q, const T* __restrict__ k,
   constexpr int RG = 256 / CPR;               // row groups
   constexpr int NR = kMaxPoolBlock / RG;      // rows per thread, at most
   __shared__ double part[2][RG][EPC][CPR];    // element e of chunk cc: consecutive cc
-  __shared__ double mean[2][D][kPoolBlocks];
-  const int c0 = blockIdx.x * kPoolBlocks;
+  __shared__ double mean[2][D][PB];
+  const int c0 = blockIdx.x * PB;
   const size_t pair = blockIdx.y;
-  const int nblk = min(kPoolBlocks, n_b - c0);
+  const int nblk = min(PB, n_b - c0);
   const int cc = threadIdx.x % CPR, rg = threadIdx.x / CPR;
   // One block in registers at a time: at 110 VGPRs three workgroups share a
   // CU (as many as the LDS holds) and hide each other's loads; a second
@@ -147,8 +155,8 @@ block_pool_kernel(const T* __restrict__ q, const T* __restrict__ k,
     }
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < 2 * D * kPoolBlocks; t += 256) {
-    const int j = t % kPoolBlocks, dd = (t / kPoolBlocks) % D, which = t / (kPoolBlocks * D);
+  for (int t = threadIdx.x; t < 2 * D * PB; t += 256) {
+    const int j = t % PB, dd = (t / PB) % D, which = t / (PB * D);
     if (j < nblk) {
       double* dst = (which == 0 ? qbar : kbar);
       dst[(pair * D + dd) * n_pad + c0 + j] = mean[which][dd][j];
@@ -429,34 +437,49 @@ void launch_mask_build(int E, dim3 grid, hipStream_t s, const double* qbar,
 void launch_select_protected(const float* sal_blk, int B, int n_b, int k_prot,
                              int32_t* prot_idx, uint8_t* prot_flag,
                              hipStream_t s) {
-  const int n_pad = next_pow2(n_b);
-  hipLaunchKernelGGL(select_protected_kernel, dim3(B), dim3(1024), 0, s, sal_blk, n_b,
-                     k_prot, n_pad, prot_idx, prot_flag);
+  hipLaunchKernelGGL(select_protected_kernel, dim3(ceil_div(n_b, kSelBlocks), B), dim3(256), 0, s,
+                     sal_blk, n_b, k_prot, prot_idx, prot_flag);
+}
+
+template <typename T, int D>
+static void launch_pool(const T* q, const T* k, double* qbar, double* kbar, int P, int L, int block,
+                        hipStream_t s) {
+  const int n_b = ceil_div(L, block);
+  const int n_pad = mask_n_pad(n_b);
+  // 8 blocks a workgroup write the means as 64-byte runs and win once the
+  // chip is full (three workgroups a CU); below that fewer blocks each spread
+  // the reads over more CUs.
+  constexpr long kFull = 3 * 256;
+#define SA_POOL(PB)                                                                            \
+  hipLaunchKernelGGL((block_pool_kernel<T, D, PB>), dim3(ceil_div(n_b, PB), P), dim3(256), 0, \
+                     s, q, k, qbar, kbar, L, block, n_b, n_pad)
+  if (static_cast<long>(ceil_div(n_b, 8)) * P >= kFull)
+    SA_POOL(8);
+  else if (static_cast<long>(ceil_div(n_b, 4)) * P >= kFull)
+    SA_POOL(4);
+  else if (static_cast<long>(ceil_div(n_b, 2)) * P >= kFull)
+    SA_POOL(2);
+  else
+    SA_POOL(1);
+#undef SA_POOL
 }
 
 void launch_block_pool(const void* q_v, const void* k_v, int B, int H, int L_v, int d,
                        int dtype, int block, double* qbar, double* kbar, hipStream_t s) {
-  const int n_b = ceil_div(L_v, block);
-  const int n_pad = mask_n_pad(n_b);
-  const dim3 pgrid(ceil_div(n_b, kPoolBlocks), B * H);
   if (dtype == 0) {
     const uint16_t* q = static_cast<const uint16_t*>(q_v);
     const uint16_t* k = static_cast<const uint16_t*>(k_v);
     if (d == 128)
-      hipLaunchKernelGGL((block_pool_kernel<uint16_t, 128>), pgrid, dim3(256), 0, s, q, k,
-                         qbar, kbar, L_v, block, n_b, n_pad);
+      launch_pool<uint16_t, 128>(q, k, qbar, kbar, B * H, L_v, block, s);
     else
-      hipLaunchKernelGGL((block_pool_kernel<uint16_t, 64>), pgrid, dim3(256), 0, s, q, k,
-                         qbar, kbar, L_v, block, n_b, n_pad);
+      launch_pool<uint16_t, 64>(q, k, qbar, kbar, B * H, L_v, block, s);
   } else {
     const float* q = static_cast<const float*>(q_v);
     const float* k = static_cast<const float*>(k_v);
     if (d == 128)
-      hipLaunchKernelGGL((block_pool_kernel<float, 128>), pgrid, dim3(256), 0, s, q, k,
-                         qbar, kbar, L_v, block, n_b, n_pad);
+      launch_pool<float, 128>(q, k, qbar, kbar, B * H, L_v, block, s);
     else
-      hipLaunchKernelGGL((block_pool_kernel<float, 64>), pgrid, dim3(256), 0, s, q, k,
-                         qbar, kbar, L_v, block, n_b, n_pad);
+      launch_pool<float, 64>(q, k, qbar, kbar, B * H, L_v, block, s);
   }
 }
 

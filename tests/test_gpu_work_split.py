@@ -1,0 +1,114 @@
+"""How a call's work is cut over the chip: every rule that picks a split by
+size (blocks per pooling workgroup, keys per saliency workgroup, parts of the
+block ranking, launch schedule of the sparse attention) at sizes on each side
+of its lines and at ragged remainders, against plain fp64 torch."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_15522_amd as sa
+from sa_parity import SAL_ABS, SAL_REL, TOL_O
+
+pytestmark = pytest.mark.gpu
+
+
+def _randn(*shape, seed, dtype=torch.bfloat16):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randn(*shape, generator=g, device="cuda").to(dtype)
+
+
+@pytest.mark.parametrize("n_b", [1, 31, 32, 33, 257, 2047, 2048])
+def test_block_ranking(n_b):
+    rng = np.random.default_rng(n_b)
+    s = rng.integers(0, max(2, n_b // 3), (2, n_b)).astype(np.float32)  # many ties
+    for k in sorted({0, 1, n_b // 3, n_b}):
+        idx, flag = sa.sa_select_protected(torch.from_numpy(s).cuda(), k)
+        for b in range(2):
+            want = np.argsort(-s[b], kind="stable")[:k]
+            assert np.array_equal(idx[b].cpu().numpy(), want), (n_b, k)
+            ref = np.zeros(n_b, np.uint8)
+            ref[want] = 1
+            assert np.array_equal(flag[b].cpu().numpy(), ref)
+
+
+# 1, 2, 4 and 8 blocks per pooling workgroup (768 workgroups are wanted)
+@pytest.mark.parametrize("H,n_b,tail,dtype", [(24, 7, 5, torch.bfloat16), (64, 24, 64, torch.bfloat16),
+                                              (64, 47, 1, torch.float32), (64, 97, 33, torch.bfloat16)])
+def test_pooled_scores(H, n_b, tail, dtype):
+    d, block = 64, 64
+    L = (n_b - 1) * block + tail
+    print(f"case pooling H={H} n_b={n_b} tail={tail} {dtype}", flush=True)
+    q, k = (_randn(1, H, L, d, seed=i, dtype=dtype) for i in (1, 2))
+    G = sa.sa_build_block_mask(q, k, 0.125, block, 1, want_scores=True)[3]
+
+    def mean(x):
+        x = torch.nn.functional.pad(x.double(), (0, 0, 0, n_b * block - L))
+        n = torch.full((n_b, 1), float(block), dtype=torch.float64, device="cuda")
+        n[-1] = tail
+        return x.view(H, n_b, block, d).sum(2) / n
+
+    ref = 0.125 * torch.stack([a @ b.T.contiguous() for a, b in zip(mean(q[0]), mean(k[0]))])
+    assert ((G[0].double() - ref).abs() <= 2.0**-24 * ref.abs() + 1e-12).all()
+
+
+# audio slabs 1 and 2; chunks of 128 to 1024 video keys, more than 16 of them
+@pytest.mark.parametrize("H,L_v,L_a,d", [(1, 2100, 40, 64), (3, 32760, 512, 128), (7, 9001, 513, 64),
+                                         (24, 16000, 70, 128)])
+def test_saliency_chunks(H, L_v, L_a, d):
+    print(f"case saliency H={H} L_v={L_v} L_a={L_a} d={d}", flush=True)
+    scale = d**-0.5
+    q_a, k_a = (_randn(1, H, L_a, d, seed=i) for i in (1, 2))
+    q_v, k_v = (_randn(1, H, L_v, d, seed=i) for i in (3, 4))
+    ref_v = torch.zeros(L_v, dtype=torch.float64, device="cuda")
+    ref_a = torch.zeros(L_a, dtype=torch.float64, device="cuda")
+    lse_a = torch.empty(1, H, L_a, device="cuda")
+    lse_v = torch.empty(1, H, L_v, device="cuda")
+    for h in range(H):
+        s = scale * (q_a[0, h].double() @ k_v[0, h].double().T.contiguous())
+        lse_a[0, h] = torch.logsumexp(s, 1)
+        ref_v += torch.softmax(s, 1).sum(0) / (H * L_a)
+        s = scale * (q_v[0, h].double() @ k_a[0, h].double().T.contiguous())
+        lse_v[0, h] = torch.logsumexp(s, 1)
+        ref_a += torch.softmax(s, 1).sum(0) / (H * L_v)
+    n_b = -(-L_v // 128)
+    ref_b = torch.nn.functional.pad(ref_v, (0, n_b * 128 - L_v)).view(n_b, 128).sum(1)
+    for got in (sa.sa_cross_scores(q_a, k_v, q_v, k_a, scale, 128),
+                sa.sa_cross_scores_from_lse(q_a, k_v, q_v, k_a, lse_a, lse_v, scale, 128),
+                sa.sa_cross_scores_pooled(q_a, k_v, q_v, k_a, scale, 128)[:3]):
+        for x, ref in zip(got, (ref_v, ref_b, ref_a)):
+            assert ((x[0].double() - ref).abs() <= SAL_REL * ref + SAL_ABS).all()
+
+
+# pair counts that are no multiple of 8, fewer than 8, and a multiple; rows on
+# both sides of what the chip holds at once; lists of every length
+@pytest.mark.parametrize("H,n_b,tail,d,block", [
+    (3, 20, 7, 128, 128), (5, 110, 128, 128, 128), (12, 87, 50, 64, 64), (8, 65, 1, 64, 128),
+    (1, 600, 64, 128, 64), (17, 31, 64, 128, 64)])
+def test_sparse_attention_schedule(H, n_b, tail, d, block):
+    L = (n_b - 1) * block + tail
+    print(f"case schedule H={H} n_b={n_b} tail={tail} d={d} block={block}", flush=True)
+    rng = np.random.default_rng(n_b)
+    idx = np.full((1, H, n_b, n_b), -1, np.int32)
+    cnt = rng.integers(0, min(n_b, 24) + 1, (1, H, n_b)).astype(np.int32)
+    cnt[0, rng.integers(0, H, 4), rng.integers(0, n_b, 4)] = n_b  # full rows
+    cnt[0, H - 1, n_b - 1] = n_b
+    for h in range(H):
+        for r in range(n_b):
+            idx[0, h, r, :cnt[0, h, r]] = np.sort(rng.permutation(n_b)[:cnt[0, h, r]])
+    q, k, v = (_randn(1, H, L, d, seed=i) for i in (1, 2, 3))
+    scale = d**-0.5
+    o, lse = sa.sa_sparse_attention(q, k, v, scale, block, torch.from_numpy(idx).cuda(),
+                                    torch.from_numpy(cnt).cuda(), want_lse=True)
+    members = torch.arange(L, device="cuda") // block
+    for h in range(H):
+        qd, kd, vd = (x[0, h].double() for x in (q, k, v))
+        for r in range(n_b):
+            rows = slice(r * block, min(L, (r + 1) * block))
+            if cnt[0, h, r] == 0:
+                assert (o[0, h, rows] == 0).all() and torch.isneginf(lse[0, h, rows]).all()
+                continue
+            keep = torch.zeros(n_b, dtype=torch.bool, device="cuda")
+            keep[torch.from_numpy(idx[0, h, r, :cnt[0, h, r]]).long().cuda()] = True
+            at = keep[members].nonzero()[:, 0]
+            p = torch.softmax(scale * (qd[rows] @ kd[at].T.contiguous()), 1)
+            assert (o[0, h, rows].double() - p @ vd[at]).abs().max() <= TOL_O["bf16"], (h, r)
