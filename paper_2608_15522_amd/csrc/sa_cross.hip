@@ -2,33 +2,34 @@
 // direction).
 //
 // a->v: s^v_i = 1/(H*L_a) * sum_h sum_j softmax_i(scale * q^a_j . k^v_i).
-//   K1 a2v_lse_partial : per (1024-key chunk, 512-query slab, b*h) one 8-wave
+//   K1 a2v_lse_partial : per (key chunk, 512-query slab, b*h) one 8-wave
 //                        workgroup holding the slab's audio queries (64 per
 //                        wave) streams the chunk's video keys with
 //                        S^T = K^v Q^a^T, so a lane owns an audio query and
 //                        keeps a lane-local (max, sum); partials go to
 //                        workspace.
 //   K1b lse_combine    : fixed-order merge of the chunk partials (log2 units).
-//   K2 a2v_colmass     : per (1024-key chunk, h, b) the workgroup streams the
+//   K2 a2v_colmass     : per (key chunk, h, b) the workgroup streams the
 //                        chunk's video keys once per audio slab with
 //                        S = Q^a K^v^T, so a lane owns a video key column and
 //                        sums exp2(S*c - lse) over its query rows; the 16
 //                        lane partials of a key are added in a fixed order.
-//   K2b a2v_finalize   : sum over heads, divide by H*L_a, block sums.
 // v->a: s^a_j = 1/(H*L_v) * sum_h sum_i softmax_j(scale * q^v_i . k^a_j).
 //   K3 v2a_colmass     : per (512 video queries, b*h); pass 1 streams every
 //                        audio key with S^T for each video query's
 //                        log-sum-exp, pass 2 streams them again, 512 at a
 //                        time, with S and sums the column mass of each key.
-//   K3b v2a_chunk_sum  : fixed-order sum over video chunks per head, then
-//       v2a_finalize   : fixed-order sum over heads, / (H*L_v).
+// Both: saliency_finalize, one launch of fixed-order sums: over heads, / (H*L_a)
+// and per block for the video map; over video chunks and heads, / (H*L_v), for
+// the audio map.
 // From the forwards: with the row LSEs of the a->v and v->a cross-attention
 // forwards (natural log, as the attention kernels write them), K1/K1b and
-// pass 1 of K3 are skipped: lse_to_log2 converts lse_a for K2, and K3 reads
-// lse_v.
+// pass 1 of K3 are skipped: K2 reads lse_a and K3 lse_v.
 // All bf16 kernels share one key-stream engine (below).  No atomics: every
 // output element has one writer, so results are reproducible.
 // fp32 inputs run the same two passes on fp32 matrix products (fp32 path below).
+#include <algorithm>
+
 #include "sa_device.h"
 #include "sa_internal.h"
 
@@ -75,7 +76,7 @@ constexpr int kGroup = 2;              // tiles per barrier interval
 constexpr int kRing = 2 * kGroup;      // stages of the LDS key ring
 static_assert(kXW * 64 == kQSlab && kXW * 64 == kV2aChunk,
               "one workgroup holds one slab of 512 query rows");
-constexpr int kColKeys = 1024;         // video keys per K2 workgroup
+constexpr int kColKeys = kMaxKeyChunk;  // video keys per K2 workgroup, at most
 constexpr int kAWin = 512;             // audio keys per K3 column-mass window
 // A log-sum-exp unit whose sum against the running max reaches 2^64 is
 // redone against its own max (the running max is only raised then).
@@ -517,14 +518,14 @@ __global__ void __launch_bounds__(kXNT) __attribute__((amdgpu_waves_per_eu(2, 2)
 a2v_lse_partial_kernel(const uint16_t* __restrict__ q_a,
                        const uint16_t* __restrict__ k_v,
                        float2* __restrict__ part, int L_v, int L_a, int nchunk,
-                       float c) {
+                       int chunk_keys, float c) {
   __shared__ __attribute__((aligned(1024))) char ring_lds[kRing * KeyRing<D>::TB];
   const int chunk = blockIdx.x, slab = blockIdx.y, pair = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 5, n = lane & 31;
   const int j0 = slab * kQSlab + wave * 64;  // first audio query row of the wave
-  const int key_begin = chunk * kLseChunk;
-  const int key_end = min(key_begin + kLseChunk, L_v);
+  const int key_begin = chunk * chunk_keys;
+  const int key_end = min(key_begin + chunk_keys, L_v);
 
   u32x4 qf[2][D / 16];
   const uint16_t* qh = q_a + static_cast<size_t>(pair) * L_a * D;
@@ -549,63 +550,80 @@ a2v_lse_partial_kernel(const uint16_t* __restrict__ q_a,
   }
 }
 
-// lse2[pair][j] = log2(sum over chunks of l * 2^m), merged in chunk order
-// (max first, then the sum); one thread per (pair, j), loads in batches of 8.
-__global__ void __launch_bounds__(64)
+// lse2[t] = log2(sum over chunks of l * 2^m) for t = (pair, j): 16 threads a
+// value merge the chunks ph, ph + 16, ... in order, then the 16 (max, sum)
+// pairs are merged in order.  One thread a value took 9 us at 64 chunks of
+// 1536 values (24 waves, two dependent passes over the chunks).
+constexpr int kCombPhases = 16;
+__global__ void __launch_bounds__(256)
 lse_combine_kernel(const float2* __restrict__ part, float* __restrict__ lse2, int P,
                    int L_a, int nchunk) {
-  const size_t t = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= static_cast<size_t>(P) * L_a) return;
-  const size_t pair = t / L_a, j = t % L_a;
-  const float2* p = part + pair * nchunk * L_a + j;
-  float M = -INFINITY;
-  for (int c0 = 0; c0 < nchunk; c0 += 8) {
-    float v[8];
+  __shared__ float2 red[kCombPhases][16];
+  const int ph = threadIdx.x >> 4, jj = threadIdx.x & 15;
+  const size_t n = static_cast<size_t>(P) * L_a;
+  const size_t t = static_cast<size_t>(blockIdx.x) * 16 + jj;
+  float M = -INFINITY, S = 0.f;
+  if (t < n) {
+    const float2* p = part + t / L_a * nchunk * L_a + t % L_a;
+    for (int c0 = ph; c0 < nchunk; c0 += 4 * kCombPhases) {
+      float2 v[4];
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      v[k] = c0 + k < nchunk ? p[static_cast<size_t>(c0 + k) * L_a].x : -INFINITY;
+      for (int k = 0; k < 4; ++k) {
+        const int c = c0 + k * kCombPhases;
+        v[k] = c < nchunk ? p[static_cast<size_t>(c) * L_a] : make_float2(-INFINITY, 0.f);
+      }
+      float m = M;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) M = fmaxf(M, v[k]);
+      for (int k = 0; k < 4; ++k) m = fmaxf(m, v[k].x);
+      float s = S > 0.f ? S * fast_exp2(M - m) : 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (v[k].y > 0.f) s += v[k].y * fast_exp2(v[k].x - m);
+      M = m;
+      S = s;
+    }
   }
-  float S = 0.f;
-  for (int c0 = 0; c0 < nchunk; c0 += 8) {
-    float2 v[8];
+  red[ph][jj] = make_float2(M, S);
+  __syncthreads();
+  if (ph != 0 || t >= n) return;
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      v[k] = c0 + k < nchunk ? p[static_cast<size_t>(c0 + k) * L_a] : make_float2(0.f, 0.f);
+  for (int k = 1; k < kCombPhases; ++k) M = fmaxf(M, red[k][jj].x);
+  S = 0.f;
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (v[k].y > 0.f) S += v[k].y * fast_exp2(v[k].x - M);
+  for (int k = 0; k < kCombPhases; ++k) {
+    const float2 v = red[k][jj];
+    if (v.y > 0.f) S += v.y * fast_exp2(v.x - M);
   }
   lse2[t] = M + __log2f(S);
 }
 
 // ---- K2 ---------------------------------------------------------------------
-// a->v column mass: grid (ceil(L_v/1024), H, B); the workgroup streams its
-// 1024 video keys once per slab of 512 audio queries (S = Q^a K^v^T, a lane
+// a->v column mass: grid (ceil(L_v/chunk_keys), H, B); the workgroup streams its
+// chunk_keys <= 1024 video keys once per slab of 512 audio queries (S = Q^a K^v^T, a lane
 // owns a key column) and adds exp2(S*c - lse) into per-lane LDS slots; the 16
 // slots of a key (8 waves x 2 lane halves) are then summed in a fixed order.
-// Keys past L_v only reach their own columns, which are not written.
+// Keys past L_v only reach their own columns, which are not written.  lse_mul
+// turns the given LSEs into log2 units.
 // POOL: the stream of the first slab also writes the block means of K^v
 // (KeyPool) to kbar ([B,H,d,n_pad]).
 template <int D, bool POOL>
 __global__ void __launch_bounds__(kXNT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 a2v_colmass_kernel(const uint16_t* __restrict__ q_a,
                    const uint16_t* __restrict__ k_v,
-                   const float* __restrict__ lse2, float* __restrict__ colmass,
-                   int H, int L_v, int L_a, float c, double* __restrict__ kbar, int block,
-                   int n_pad) {
+                   const float* __restrict__ lse, float lse_mul, float* __restrict__ colmass,
+                   int H, int L_v, int L_a, int chunk_keys, float c, double* __restrict__ kbar,
+                   int block, int n_pad) {
   constexpr int RS = kColKeys + 32;  // slot row stride (the two lane halves use different banks)
   __shared__ __attribute__((aligned(1024))) char ring_lds[kRing * KeyRing<D>::TB];
   __shared__ float red[2 * kXW][RS];
   const int chunk = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 5, n = lane & 31;
-  const int key_begin = chunk * kColKeys;
-  const int key_end = min(key_begin + kColKeys, L_v);
+  const int key_begin = chunk * chunk_keys;
+  const int key_end = min(key_begin + chunk_keys, L_v);
   const size_t pair = static_cast<size_t>(b) * H + h;
   const uint16_t* qh = q_a + pair * L_a * D;
-  const float* lh = lse2 + pair * L_a;
+  const float* lh = lse + pair * L_a;
   const char* kh = reinterpret_cast<const char*>(k_v + pair * L_v * D);
   const int T = ceil_div(key_end - key_begin, 64);
 
@@ -614,20 +632,25 @@ a2v_colmass_kernel(const uint16_t* __restrict__ q_a,
   ColAcc<D> acc;
   acc.c = c;
   acc.red = &red[2 * wave + g][n];
-  for (int k = 0; k < kColKeys; k += 32) acc.red[k] = 0.f;  // the lane's own slots
+#pragma unroll 4
+  for (int k = 0; k < chunk_keys; k += 32) acc.red[k] = 0.f;  // the lane's own slots
 
   for (int slab = 0; slab * kQSlab < L_a; ++slab) {
     const int j0 = slab * kQSlab + wave * 64;
     u32x4 qf[2][D / 16];
     load_qfrag<D>(qh, j0 + n, L_a, g, qf[0]);
     load_qfrag<D>(qh, j0 + 32 + n, L_a, g, qf[1]);
+    // unconditional loads at clamped rows, so that all 32 are in flight at once
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int jj = j0 + 32 * hh + crow(i, g);
-        acc.lr[hh][i] = jj < L_a ? lh[jj] : INFINITY;
-      }
+      for (int i = 0; i < 16; ++i)
+        acc.lr[hh][i] = lh[min(j0 + 32 * hh + crow(i, g), L_a - 1)];
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        acc.lr[hh][i] = j0 + 32 * hh + crow(i, g) < L_a ? acc.lr[hh][i] * lse_mul : INFINITY;
     if (POOL && slab == 0) {
       ColPoolAcc<D> pacc;
       static_cast<ColAcc<D>&>(pacc) = acc;
@@ -638,7 +661,7 @@ a2v_colmass_kernel(const uint16_t* __restrict__ q_a,
       stream_keys<D, false>(ring, ring_lds, kh, key_begin, L_v, T, qf, acc);
     }
   }
-  for (int k = threadIdx.x; k < kColKeys; k += kXNT) {
+  for (int k = threadIdx.x; k < chunk_keys; k += kXNT) {
     float sum = 0.f;
 #pragma unroll
     for (int w = 0; w < 2 * kXW; ++w) sum += red[w][k];
@@ -733,69 +756,92 @@ v2a_colmass_kernel(const uint16_t* __restrict__ q_v,
 }
 
 // ---- finalize ---------------------------------------------------------------
-// sal_v_tok / sal_v_blk from column-mass partials [B][nsum][L_v] (per head,
-// or one partial holding every head), summed in order: grid (n_b, B), block
-// threads = `block` (one per token of the video block).
-__global__ void __launch_bounds__(128)
-a2v_finalize_kernel(const float* __restrict__ colmass, float* __restrict__ sal_v_tok,
-                    float* __restrict__ sal_v_blk, int L_v, int nsum,
-                    float inv_norm, int accumulate) {
-  __shared__ float red[128];
-  const int c = blockIdx.x, b = blockIdx.y, n_b = gridDim.x;
-  const int i = c * blockDim.x + threadIdx.x;
-  float v = 0.f;
-  if (i < L_v) {
-    v = sum_strided(colmass + static_cast<size_t>(b) * nsum * L_v + i, L_v, nsum);
-    v *= inv_norm;
-    if (sal_v_tok != nullptr) {
-      float* dst = sal_v_tok + static_cast<size_t>(b) * L_v + i;
-      *dst = accumulate ? *dst + v : v;
-    }
-  }
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (static_cast<int>(threadIdx.x) < s) red[threadIdx.x] += red[threadIdx.x + s];
+// Both directions' sums in one launch of 1024-thread workgroups.
+//  [0, B * n_b): sal_v_tok and sal_v_blk of one video block from the column
+//    masses [B][H][L_v]: thread (ph, t) adds the heads ph, ph + NP, ... of
+//    token t in order (NP = 1024 / block phases), the phases are added in
+//    order, then the tokens by a tree.
+//  the rest: sal_a_tok of 16 audio tokens from v2a_part [B][nparts][L_a]:
+//    64 phases a token, added in phase order.
+constexpr int kFinThreads = 1024;
+constexpr int kFinAud = 16;  // audio tokens per workgroup
+__global__ void __launch_bounds__(kFinThreads)
+saliency_finalize_kernel(const float* __restrict__ colmass, float* __restrict__ sal_v_tok,
+                         float* __restrict__ sal_v_blk, int B, int H, int L_v, int block,
+                         float inv_norm_v, const float* __restrict__ v2a_part,
+                         float* __restrict__ sal_a_tok, int nparts, int L_a, float inv_norm_a,
+                         int accumulate) {
+  __shared__ float red[kFinThreads];
+  const int tid = threadIdx.x, n_b = ceil_div(L_v, block);
+  if (static_cast<int>(blockIdx.x) < B * n_b) {
+    const int c = blockIdx.x % n_b, b = blockIdx.x / n_b;
+    const int NP = kFinThreads / block, ph = tid / block, t = tid % block;
+    const int i = c * block + t;
+    float v = 0.f;
+    if (i < L_v && ph < H)
+      v = sum_strided(colmass + (static_cast<size_t>(b) * H + ph) * L_v + i,
+                      static_cast<size_t>(NP) * L_v, (H - ph + NP - 1) / NP);
+    red[tid] = v;
     __syncthreads();
+    if (tid < block) {
+      for (int p = 1; p < NP; ++p) v += red[p * block + tid];
+      v *= inv_norm_v;
+      if (i < L_v && sal_v_tok != nullptr) {
+        float* dst = sal_v_tok + static_cast<size_t>(b) * L_v + i;
+        *dst = accumulate ? *dst + v : v;
+      }
+      red[tid] = v;
+    }
+    __syncthreads();
+    for (int s = block / 2; s > 0; s >>= 1) {
+      if (tid < s) red[tid] += red[tid + s];
+      __syncthreads();
+    }
+    if (tid == 0) {
+      float* dst = sal_v_blk + static_cast<size_t>(b) * n_b + c;
+      *dst = accumulate ? *dst + red[0] : red[0];
+    }
+    return;
   }
-  if (threadIdx.x == 0) {
-    float* dst = sal_v_blk + static_cast<size_t>(b) * n_b + c;
-    *dst = accumulate ? *dst + red[0] : red[0];
-  }
-}
-
-// head_sum[pair][j] = sum over video chunks of part[pair][chunk][j]: grid
-// (ceil(L_a/64), P), 256 threads = 4 chunk phases x 64 audio keys, then a
-// fixed-order sum of the 4 phases.
-__global__ void __launch_bounds__(256)
-v2a_chunk_sum_kernel(const float* __restrict__ part, float* __restrict__ head_sum,
-                     int L_a, int nchunk) {
-  __shared__ float red[4][64];
-  const int j = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int ph = threadIdx.x >> 6;
-  const size_t pair = blockIdx.y;
+  const int w = blockIdx.x - B * n_b, nat = ceil_div(L_a, kFinAud);
+  const int b = w / nat, j = (w % nat) * kFinAud + tid % kFinAud;
+  constexpr int NP = kFinThreads / kFinAud;
+  const int ph = tid / kFinAud;
   float v = 0.f;
-  if (j < L_a && ph < nchunk)
-    v = sum_strided(part + (pair * nchunk + ph) * L_a + j, 4 * static_cast<size_t>(L_a),
-                    (nchunk - ph + 3) / 4);
-  red[ph][threadIdx.x & 63] = v;
+  if (j < L_a && ph < nparts)
+    v = sum_strided(v2a_part + (static_cast<size_t>(b) * nparts + ph) * L_a + j,
+                    static_cast<size_t>(NP) * L_a, (nparts - ph + NP - 1) / NP);
+  red[tid] = v;
   __syncthreads();
-  if (ph == 0 && j < L_a)
-    head_sum[pair * L_a + j] = (red[0][threadIdx.x] + red[1][threadIdx.x]) +
-                               (red[2][threadIdx.x] + red[3][threadIdx.x]);
+  // 8 threads a token add 8 phases each, the first of them those 8 sums
+  if (tid < 8 * kFinAud) {
+    const int g = tid / kFinAud;
+    v = 0.f;
+    for (int p = 0; p < NP / 8; ++p) v += red[(g * (NP / 8) + p) * kFinAud + tid % kFinAud];
+  }
+  __syncthreads();
+  red[tid] = v;
+  __syncthreads();
+  if (tid < kFinAud && j < L_a) {
+    v = 0.f;
+    for (int g = 0; g < 8; ++g) v += red[g * kFinAud + tid];
+    v *= inv_norm_a;
+    float* dst = sal_a_tok + static_cast<size_t>(b) * L_a + j;
+    *dst = accumulate ? *dst + v : v;
+  }
 }
 
-// sal_a_tok[b][j] = sum over nparts of part / (H*L_v), fixed order.
-__global__ void v2a_finalize_kernel(const float* __restrict__ part,
-                                    float* __restrict__ sal_a_tok, int B,
-                                    int nparts, int L_a, float inv_norm,
-                                    int accumulate) {
-  const size_t t = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= static_cast<size_t>(B) * L_a) return;
-  const size_t b = t / L_a, j = t % L_a;
-  float v = sum_strided(part + b * nparts * L_a + j, L_a, nparts);
-  v *= inv_norm;
-  sal_a_tok[t] = accumulate ? sal_a_tok[t] + v : v;
+// sal_a_tok == NULL: the a->v direction only.
+void launch_finalize(const float* colmass, float* sal_v_tok, float* sal_v_blk, int B, int H,
+                     int L_v, int block, const float* v2a_part, float* sal_a_tok, int nchunk3,
+                     int L_a, int accumulate, hipStream_t s) {
+  const int n_v = B * ceil_div(L_v, block);
+  const int n_a = sal_a_tok != nullptr ? B * ceil_div(L_a, kFinAud) : 0;
+  hipLaunchKernelGGL(saliency_finalize_kernel, dim3(n_v + n_a), dim3(kFinThreads), 0, s, colmass,
+                     sal_v_tok, sal_v_blk, B, H, L_v, block,
+                     1.0f / (static_cast<float>(H) * static_cast<float>(L_a)), v2a_part, sal_a_tok,
+                     H * nchunk3, L_a, 1.0f / (static_cast<float>(H) * static_cast<float>(L_v)),
+                     accumulate);
 }
 
 // ---- fp32 path --------------------------------------------------------------
@@ -977,19 +1023,69 @@ colmass_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
   }
 }
 
+// Video keys per K1 or K2 workgroup: the multiple of 128 (whole blocks) up to
+// kMaxKeyChunk that takes least time by rounds of the 256 workgroups that run
+// at once (one per CU), a round lasting as many tiles as the chunk has plus
+// kFill for the query slab's load and the pipeline's fill; `max_chunks` bounds
+// their number (the room for K1's partials).  1024 keys leave a call of few
+// heads or short clips on part of the chip (96 workgroups at H3 L_v32760).
+int key_chunk(int L_v, long per_chunk, long max_chunks) {
+  constexpr int kFill = 3;
+  int best = kMaxKeyChunk;
+  long best_cost = 0;
+  for (int ck = kMaxKeyChunk; ck >= 128; ck -= 128) {
+    const long n = ceil_div(L_v, ck);
+    if (n > max_chunks) break;
+    const long cost = (n * per_chunk + 255) / 256 * (std::min(ck, L_v) / 64 + kFill);
+    if (ck == kMaxKeyChunk || cost < best_cost) {
+      best = ck;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 // K2, with the block means of K^v written to kbar when it is not NULL.
 template <int D>
-void launch_a2v_colmass(const uint16_t* q_a, const uint16_t* k_v, const float* lse2,
+void launch_a2v_colmass(const uint16_t* q_a, const uint16_t* k_v, const float* lse, float lse_mul,
                         float* colmass, int B, int H, int L_v, int L_a, float c, double* kbar,
                         int block, hipStream_t s) {
-  const dim3 grid(ceil_div(L_v, kColKeys), H, B);
+  const int ck = key_chunk(L_v, static_cast<long>(B) * H, L_v);
+  const dim3 grid(ceil_div(L_v, ck), H, B);
   const int n_pad = mask_n_pad(ceil_div(L_v, block));
   if (kbar != nullptr)
-    hipLaunchKernelGGL((a2v_colmass_kernel<D, true>), grid, dim3(kXNT), 0, s, q_a, k_v, lse2,
-                       colmass, H, L_v, L_a, c, kbar, block, n_pad);
+    hipLaunchKernelGGL((a2v_colmass_kernel<D, true>), grid, dim3(kXNT), 0, s, q_a, k_v, lse,
+                       lse_mul, colmass, H, L_v, L_a, ck, c, kbar, block, n_pad);
   else
-    hipLaunchKernelGGL((a2v_colmass_kernel<D, false>), grid, dim3(kXNT), 0, s, q_a, k_v, lse2,
-                       colmass, H, L_v, L_a, c, kbar, block, n_pad);
+    hipLaunchKernelGGL((a2v_colmass_kernel<D, false>), grid, dim3(kXNT), 0, s, q_a, k_v, lse,
+                       lse_mul, colmass, H, L_v, L_a, ck, c, kbar, block, n_pad);
+}
+
+// The two column-mass passes and the sums, from the a->v row LSEs (times
+// lse_mul in log2 units) and, when lse_v is not NULL, the v->a ones (natural
+// log); otherwise K3 forms its own.
+template <int D>
+void column_masses(const uint16_t* q_a, const uint16_t* k_v, const uint16_t* q_v,
+                   const uint16_t* k_a, const float* lse_a, float lse_mul, const float* lse_v,
+                   int B, int H, int L_v, int L_a, float c, int block, float* sal_v_tok,
+                   float* sal_v_blk, float* sal_a_tok, int accumulate, double* qbar, double* kbar,
+                   const CrossWs& lay, char* ws, hipStream_t s) {
+  float* colmass = reinterpret_cast<float*>(ws + lay.colmass);
+  float* v2a_part = reinterpret_cast<float*>(ws + lay.v2a_part);
+  launch_a2v_colmass<D>(q_a, k_v, lse_a, lse_mul, colmass, B, H, L_v, L_a, c, kbar, block, s);
+  const int nchunk3 = ceil_div(L_v, kV2aChunk);
+  if (q_v != nullptr) {
+    const dim3 grid(nchunk3, 1, B * H);
+    const int n_pad = mask_n_pad(ceil_div(L_v, block));
+    if (lse_v != nullptr)
+      hipLaunchKernelGGL((v2a_colmass_kernel<D, true>), grid, dim3(kXNT), 0, s, q_v, k_a, v2a_part,
+                         L_v, L_a, nchunk3, c, lse_v, qbar, block, n_pad);
+    else
+      hipLaunchKernelGGL((v2a_colmass_kernel<D, false>), grid, dim3(kXNT), 0, s, q_v, k_a,
+                         v2a_part, L_v, L_a, nchunk3, c, nullptr, qbar, block, n_pad);
+  }
+  launch_finalize(colmass, sal_v_tok, sal_v_blk, B, H, L_v, block, v2a_part,
+                  q_v != nullptr ? sal_a_tok : nullptr, nchunk3, L_a, accumulate, s);
 }
 
 template <int D>
@@ -1000,44 +1096,22 @@ void cross_bf16(const uint16_t* q_a, const uint16_t* k_v, const uint16_t* q_v,
   const CrossWs lay = cross_ws_layout(B, H, L_v, L_a);
   const float c = scale * kLog2e;
   const int P = B * H;
-  const int nchunk = ceil_div(L_v, kLseChunk);
   const int nslab = ceil_div(L_a, kQSlab);
+  // K1's partials may fill the workspace up to v2a_head: nothing in that part
+  // is in use before lse_combine has read them, and its result goes to
+  // v2a_head, which the bf16 path does not need otherwise.
   float2* lse_part = reinterpret_cast<float2*>(ws + lay.lse_part);
-  float* lse_a = reinterpret_cast<float*>(ws + lay.lse_a);
-  float* colmass = reinterpret_cast<float*>(ws + lay.colmass);
-  hipLaunchKernelGGL(a2v_lse_partial_kernel<D>, dim3(nchunk, nslab, P), dim3(kXNT), 0, s,
-                     q_a, k_v, lse_part, L_v, L_a, nchunk, c);
+  float* lse_a = reinterpret_cast<float*>(ws + lay.v2a_head);
   const size_t nlse = static_cast<size_t>(P) * L_a;
-  hipLaunchKernelGGL(lse_combine_kernel, dim3((nlse + 63) / 64), dim3(64), 0, s,
+  const long max_chunks = static_cast<long>((lay.v2a_head - lay.lse_part) / (sizeof(float2) * nlse));
+  const int ck = key_chunk(L_v, static_cast<long>(nslab) * P, max_chunks);
+  const int nchunk = ceil_div(L_v, ck);
+  hipLaunchKernelGGL(a2v_lse_partial_kernel<D>, dim3(nchunk, nslab, P), dim3(kXNT), 0, s,
+                     q_a, k_v, lse_part, L_v, L_a, nchunk, ck, c);
+  hipLaunchKernelGGL(lse_combine_kernel, dim3((nlse + 15) / 16), dim3(256), 0, s,
                      lse_part, lse_a, P, L_a, nchunk);
-  launch_a2v_colmass<D>(q_a, k_v, lse_a, colmass, B, H, L_v, L_a, c, kbar, block, s);
-  const int n_b = ceil_div(L_v, block);
-  hipLaunchKernelGGL(a2v_finalize_kernel, dim3(n_b, B), dim3(block), 0, s, colmass,
-                     sal_v_tok, sal_v_blk, L_v, H,
-                     1.0f / (static_cast<float>(H) * static_cast<float>(L_a)), accumulate);
-  if (q_v != nullptr) {
-    float* v2a_part = reinterpret_cast<float*>(ws + lay.v2a_part);
-    const int nchunk3 = ceil_div(L_v, kV2aChunk);
-    float* v2a_head = reinterpret_cast<float*>(ws + lay.v2a_head);
-    hipLaunchKernelGGL((v2a_colmass_kernel<D, false>), dim3(nchunk3, 1, P),
-                       dim3(kXNT), 0, s, q_v, k_a, v2a_part, L_v, L_a, nchunk3, c, nullptr,
-                       qbar, block, mask_n_pad(ceil_div(L_v, block)));
-    hipLaunchKernelGGL(v2a_chunk_sum_kernel, dim3(ceil_div(L_a, 64), P), dim3(256), 0, s,
-                       v2a_part, v2a_head, L_a, nchunk3);
-    const size_t na = static_cast<size_t>(B) * L_a;
-    hipLaunchKernelGGL(v2a_finalize_kernel, dim3((na + 255) / 256), dim3(256), 0, s,
-                       v2a_head, sal_a_tok, B, H, L_a,
-                       1.0f / (static_cast<float>(H) * static_cast<float>(L_v)), accumulate);
-  }
-}
-
-// lse2 = lse * log2(e): natural-log LSE of the scaled scores to the log2
-// units of the key-stream kernels.
-__global__ void __launch_bounds__(256)
-lse_to_log2_kernel(const float* __restrict__ lse, float* __restrict__ lse2, size_t n) {
-  for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
-       i += static_cast<size_t>(gridDim.x) * 256)
-    lse2[i] = lse[i] * kLog2e;
+  column_masses<D>(q_a, k_v, q_v, k_a, lse_a, 1.f, nullptr, B, H, L_v, L_a, c, block, sal_v_tok,
+                   sal_v_blk, sal_a_tok, accumulate, qbar, kbar, lay, ws, s);
 }
 
 // The saliency of both directions from the row LSEs of the two cross-
@@ -1048,34 +1122,9 @@ void cross_bf16_from_lse(const uint16_t* q_a, const uint16_t* k_v, const uint16_
                          int H, int L_v, int L_a, float scale, int block, float* sal_v_tok,
                          float* sal_v_blk, float* sal_a_tok, int accumulate, double* qbar,
                          double* kbar, char* ws, hipStream_t s) {
-  const CrossWs lay = cross_ws_layout(B, H, L_v, L_a);
-  const float c = scale * kLog2e;
-  const int P = B * H;
-  float* lse2 = reinterpret_cast<float*>(ws + lay.lse_a);
-  float* colmass = reinterpret_cast<float*>(ws + lay.colmass);
-  const size_t nlse = static_cast<size_t>(P) * L_a;
-  const size_t cblocks = (nlse + 255) / 256;
-  hipLaunchKernelGGL(lse_to_log2_kernel, dim3(static_cast<unsigned>(cblocks < 1024 ? cblocks : 1024)),
-                     dim3(256), 0, s, lse_a, lse2, nlse);
-  launch_a2v_colmass<D>(q_a, k_v, lse2, colmass, B, H, L_v, L_a, c, kbar, block, s);
-  const int n_b = ceil_div(L_v, block);
-  hipLaunchKernelGGL(a2v_finalize_kernel, dim3(n_b, B), dim3(block), 0, s, colmass,
-                     sal_v_tok, sal_v_blk, L_v, H,
-                     1.0f / (static_cast<float>(H) * static_cast<float>(L_a)), accumulate);
-  if (q_v != nullptr) {
-    float* v2a_part = reinterpret_cast<float*>(ws + lay.v2a_part);
-    const int nchunk3 = ceil_div(L_v, kV2aChunk);
-    float* v2a_head = reinterpret_cast<float*>(ws + lay.v2a_head);
-    hipLaunchKernelGGL((v2a_colmass_kernel<D, true>), dim3(nchunk3, 1, P),
-                       dim3(kXNT), 0, s, q_v, k_a, v2a_part, L_v, L_a, nchunk3, c, lse_v,
-                       qbar, block, mask_n_pad(ceil_div(L_v, block)));
-    hipLaunchKernelGGL(v2a_chunk_sum_kernel, dim3(ceil_div(L_a, 64), P), dim3(256), 0, s,
-                       v2a_part, v2a_head, L_a, nchunk3);
-    const size_t na = static_cast<size_t>(B) * L_a;
-    hipLaunchKernelGGL(v2a_finalize_kernel, dim3((na + 255) / 256), dim3(256), 0, s,
-                       v2a_head, sal_a_tok, B, H, L_a,
-                       1.0f / (static_cast<float>(H) * static_cast<float>(L_v)), accumulate);
-  }
+  column_masses<D>(q_a, k_v, q_v, k_a, lse_a, kLog2e, lse_v, B, H, L_v, L_a, scale * kLog2e,
+                   block, sal_v_tok, sal_v_blk, sal_a_tok, accumulate, qbar, kbar,
+                   cross_ws_layout(B, H, L_v, L_a), ws, s);
 }
 
 template <int D>
@@ -1091,7 +1140,6 @@ void cross_f32(const float* q_a, const float* k_v, const float* q_v,
   float* colmass = reinterpret_cast<float*>(ws + lay.colmass);
   float* lse_v = reinterpret_cast<float*>(ws + lay.lse_v);
   float* v2a_part = reinterpret_cast<float*>(ws + lay.v2a_part);
-  float* v2a_head = reinterpret_cast<float*>(ws + lay.v2a_head);
   // Log2-sum-exps: a->v in chunks of 1024 video keys (merged below), v->a
   // over all audio keys at once.
   const int nchunk = ceil_div(L_v, kLseChunk);
@@ -1107,7 +1155,7 @@ void cross_f32(const float* q_a, const float* k_v, const float* q_v,
                      v, c);
   if (nchunk > 1) {
     const size_t nlse = static_cast<size_t>(P) * L_a;
-    hipLaunchKernelGGL(lse_combine_kernel, dim3((nlse + 63) / 64), dim3(64), 0, s, lse_part, lse_a,
+    hipLaunchKernelGGL(lse_combine_kernel, dim3((nlse + 15) / 16), dim3(256), 0, s, lse_part, lse_a,
                        P, L_a, nchunk);
   }
   // Column masses: a->v over all audio queries, v->a in chunks of 512 video
@@ -1119,18 +1167,8 @@ void cross_f32(const float* q_a, const float* k_v, const float* q_v,
   if (q_v == nullptr) v.n_wg = 0;
   hipLaunchKernelGGL(colmass_f32_kernel<D>, dim3(a.n_wg + v.n_wg, P), dim3(64 * kF32XWaves), 0, s, a,
                      v, c);
-  const int n_b = ceil_div(L_v, block);
-  hipLaunchKernelGGL(a2v_finalize_kernel, dim3(n_b, B), dim3(block), 0, s, colmass,
-                     sal_v_tok, sal_v_blk, L_v, H,
-                     1.0f / (static_cast<float>(H) * static_cast<float>(L_a)), accumulate);
-  if (q_v != nullptr) {
-    hipLaunchKernelGGL(v2a_chunk_sum_kernel, dim3(ceil_div(L_a, 64), P), dim3(256), 0, s,
-                       v2a_part, v2a_head, L_a, nchunk3);
-    const size_t na = static_cast<size_t>(B) * L_a;
-    hipLaunchKernelGGL(v2a_finalize_kernel, dim3((na + 255) / 256), dim3(256), 0, s,
-                       v2a_head, sal_a_tok, B, H, L_a,
-                       1.0f / (static_cast<float>(H) * static_cast<float>(L_v)), accumulate);
-  }
+  launch_finalize(colmass, sal_v_tok, sal_v_blk, B, H, L_v, block, v2a_part,
+                  q_v != nullptr ? sal_a_tok : nullptr, nchunk3, L_a, accumulate, s);
 }
 
 }  // namespace

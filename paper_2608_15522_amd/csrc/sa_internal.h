@@ -10,7 +10,9 @@
 namespace sa {
 
 // Tunables fixed at build time.
-constexpr int kLseChunk = 1024;   // video keys per a->v log-sum-exp partial
+constexpr int kLseChunk = 1024;   // video keys per a->v log-sum-exp partial that the
+                                  // workspace holds room for (fp32 path: the chunk)
+constexpr int kMaxKeyChunk = 1024;  // most video keys of an a->v workgroup, bf16 path
 constexpr int kQSlab = 512;       // queries per 16-wave workgroup slab
 constexpr int kV2aChunk = 512;    // video queries per v->a workgroup
 constexpr int kMaxBlocks = 2048;  // largest supported n_b
@@ -21,11 +23,11 @@ inline size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 // Workspace of sa_cross_scores (both dtypes are covered).
 struct CrossWs {
   size_t lse_part;   // float2 [B,H,nchunk,L_a]  (m, l) partials, bf16 path
-  size_t lse_a;      // float  [B,H,L_a]         a->v log2-sum-exp
+  size_t lse_a;      // float  [B,H,L_a]         a->v log2-sum-exp, f32 path
   size_t colmass;    // float  [B,H,L_v]         per-head a->v column mass
   size_t lse_v;      // float  [B,H,L_v]         v->a log2-sum-exp, f32 path
   size_t v2a_part;   // float  [B,H,nchunk3,L_a] v->a column-mass partials
-  size_t v2a_head;   // float  [B,H,L_a]         the same summed over chunks
+  size_t v2a_head;   // float  [B,H,L_a]         a->v log2-sum-exp, bf16 path
   size_t total;
 };
 
