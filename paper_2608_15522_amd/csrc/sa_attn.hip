@@ -20,12 +20,11 @@
 // only when a lane's max grows by more than 2^8.  Keys past L are -inf, rows
 // past L are never written.
 //
-// Query blocks of a (batch, head) pair are launched heaviest list first
-// (protected rows hold the full list).  With a pair count that is a multiple
-// of 8, each XCD takes every 8th pair: first the full rows of all its pairs,
-// then the other rows one pair at a time, so that a pair's K/V blocks are
-// shared through one XCD's L2 and the long full rows do not run alone at the
-// end of the launch; otherwise the launch is rank-major over pairs.
+// Rows beyond what the chip holds at once go through a launch schedule: each
+// XCD takes every 8th (batch, head) pair, first the full rows of all its pairs
+// (protected rows hold the full list), then the other rows one pair at a time,
+// so that a pair's K/V blocks are shared through one XCD's L2 and the long full
+// rows do not run alone at the end of the launch.
 //
 // Gather form: dense rows gathered by index (protected tokens) or all rows
 // of a query tensor of another length (cross-modal attention), every key
@@ -45,93 +44,100 @@ namespace {
 constexpr int kTile = 64;       // keys per LDS tile
 constexpr int kCusPerXcd = 32;  // MI355X: 8 XCDs of 32 CUs
 
-// Query blocks of every (b,h) pair ordered by kv_cnt descending, then by
-// block index ascending.  Each block gets the key (n_b - cnt) * 4096 + index,
-// unique and in that order, and its rank is the number of smaller keys.
-// Grid (pairs, ceil(n_b / kOrderRows)): every workgroup loads the pair's keys
-// into LDS and ranks kOrderRows of its blocks, reading the keys four at a time
-// (entries past n_b hold INT_MAX and never count).
-constexpr int kOrderRows = 256;
-__global__ void __launch_bounds__(kOrderRows)
-order_rows_kernel(const int32_t* __restrict__ kv_cnt, int32_t* __restrict__ order,
-                  int n_b) {
-  __shared__ __attribute__((aligned(16))) int key[kMaxBlocks];
-  const size_t base = static_cast<size_t>(blockIdx.x) * n_b;
-  const int n4 = ceil_div(n_b, 4);
-  for (int r = threadIdx.x; r < 4 * n4; r += blockDim.x) {
-    int k = 0x7fffffff;
-    if (r < n_b) {
-      int c = kv_cnt[base + r];
-      c = c < 0 ? 0 : (c > n_b ? n_b : c);
-      k = (n_b - c) * 4096 + r;
-    }
-    key[r] = k;
-  }
-  __syncthreads();
-  const int r = blockIdx.y * kOrderRows + threadIdx.x;
-  if (r >= n_b) return;
-  const int mine = key[r];
-  const int4* k4 = reinterpret_cast<const int4*>(key);
-  int rk[4] = {0, 0, 0, 0};
-#pragma unroll 4
-  for (int j4 = 0; j4 < n4; ++j4) {
-    const int4 o = k4[j4];
-    rk[0] += o.x < mine;
-    rk[1] += o.y < mine;
-    rk[2] += o.z < mine;
-    rk[3] += o.w < mine;
-  }
-  order[base + (rk[0] + rk[1]) + (rk[2] + rk[3])] = r;
+// Launch schedule.  Workgroup w runs on XCD w % 8, which owns the pairs x,
+// x+8, x+16, ... (b,h); entry i of XCD x's list (pair << 11 | query block) is
+// one row of work.  The list holds first the full rows (lists of all n_b key
+// blocks: the protected query blocks) of every pair the XCD owns, pair by
+// pair, then the other rows pair by pair, each pair's rows in eight classes of
+// list length, longest first, by index within a class.  A full row takes
+// n_b / k_keep times as long as the others; started first, the full rows of
+// the XCD's last pairs do not run alone at the end of the launch, while the
+// other rows still go through one pair at a time, so that their K/V blocks are
+// shared through the XCD's L2.
+// One workgroup per XCD, one wave per pair at a time (ballot counts, two
+// barriers in all).  Ranking every row exactly in a kernel of its own first
+// and writing the lists in a second took 5 + 6 us at P = 24, n_b = 256; this
+// one takes about 6.
+constexpr int kXcds = 8;
+constexpr int kLenClasses = 8;
+__host__ __device__ constexpr int xcd_pairs(int P, int x) { return (P - x + kXcds - 1) / kXcds; }
+// Pairs of the XCDs before x: their lists come first in `sched`.
+__host__ __device__ constexpr int xcd_first(int P, int x) {
+  const int q = P / kXcds, rem = P % kXcds;
+  return x * q + (x < rem ? x : rem);
 }
 
-// Launch schedule when the pair count is a multiple of 8.  Workgroup w runs
-// on XCD w % 8, which owns the pairs x, x+8, x+16, ...; entry i of XCD x's
-// list (pair << 11 | query block) is the work of its workgroup 8*i + x.  The
-// list holds first the full rows (lists of all n_b key blocks: the protected
-// query blocks) of every pair the XCD owns, pair by pair, then the other rows
-// pair by pair, each pair's rows in launch order (heaviest list first).  A
-// full row takes n_b / k_keep times as long as the others; started first, the
-// full rows of the XCD's last pairs no longer run alone at the end of the
-// launch, while the other rows still go through one pair at a time, so that
-// their K/V blocks are shared through the XCD's L2.
 __global__ void __launch_bounds__(1024)
-schedule_rows_kernel(const int32_t* __restrict__ kv_cnt, const int32_t* __restrict__ order,
-                     int32_t* __restrict__ sched, int* __restrict__ claim, int P, int n_b) {
-  __shared__ int nfull[kMaxPairs / 8 + 1];
-  __shared__ int total_full;
-  const int x = blockIdx.x, np = P >> 3, tid = threadIdx.x;
+schedule_rows_kernel(const int32_t* __restrict__ kv_cnt, int32_t* __restrict__ sched,
+                     int* __restrict__ claim, int P, int n_b) {
+  __shared__ int full_before[kMaxPairs / kXcds + 2];  // full rows of the list's earlier pairs
+  const int x = blockIdx.x, np = xcd_pairs(P, x), tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  constexpr int NW = 1024 / 64;
   if (tid == 0) claim[64 * x] = 0;  // the attention kernel's row counter of XCD x
-  for (int j = 0; j < np; ++j) {
-    const size_t base = static_cast<size_t>(x + 8 * j) * n_b;
+  const uint64_t lanes_below = (1ull << lane) - 1ull;
+  for (int j = wave; j < np; j += NW) {
+    const int32_t* cnt = kv_cnt + static_cast<size_t>(x + kXcds * j) * n_b;
     int nf = 0;
-    for (int r0 = 0; r0 < n_b; r0 += blockDim.x) {
-      const int r = r0 + tid;
-      nf += __syncthreads_count(r < n_b && kv_cnt[base + r] >= n_b);
-    }
-    if (tid == 0) nfull[j] = nf;
+    for (int r0 = 0; r0 < n_b; r0 += 64)
+      nf += __popcll(__ballot(r0 + lane < n_b && cnt[min(r0 + lane, n_b - 1)] >= n_b));
+    if (lane == 0) full_before[j + 1] = nf;
   }
   __syncthreads();
-  if (tid == 0) {  // exclusive prefix over the pairs, in pair order
+  if (wave == 0) {  // prefix over the pairs, in pair order
     int acc = 0;
-    for (int j = 0; j < np; ++j) {
-      const int nf = nfull[j];
-      nfull[j] = acc;
-      acc += nf;
+    for (int j0 = 0; j0 < np; j0 += 64) {
+      int v = j0 + lane < np ? full_before[j0 + lane + 1] : 0;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(v, o, 64);
+        if (lane >= o) v += u;
+      }
+      if (j0 + lane < np) full_before[j0 + lane + 1] = acc + v;
+      acc += __shfl(v, 63, 64);
     }
-    nfull[np] = acc;
-    total_full = acc;
+    if (lane == 0) full_before[0] = 0;
   }
   __syncthreads();
-  int32_t* out = sched + static_cast<size_t>(x) * np * n_b;
-  const int F = total_full;
-  for (int j = 0; j < np; ++j) {
-    const int pair = x + 8 * j;
-    const size_t base = static_cast<size_t>(pair) * n_b;
-    const int fpre = nfull[j], nf = nfull[j + 1] - fpre;
-    const int rest_pre = j * n_b - fpre;  // other rows of the earlier pairs
-    for (int rank = tid; rank < n_b; rank += blockDim.x) {
-      const int pos = rank < nf ? fpre + rank : F + rest_pre + (rank - nf);
-      out[pos] = (pair << 11) | order[base + rank];
+  int32_t* out = sched + static_cast<size_t>(xcd_first(P, x)) * n_b;
+  const int F = full_before[np];
+  for (int j = wave; j < np; j += NW) {
+    const int pair = x + kXcds * j;
+    const int32_t* cnt = kv_cnt + static_cast<size_t>(pair) * n_b;
+    // class of a row: -1 full, else 0 (longest) .. kLenClasses - 1
+    auto row_class = [&](int r) {
+      const int c = max(cnt[min(r, n_b - 1)], 0);
+      return c >= n_b ? -1 : kLenClasses - 1 - c * kLenClasses / n_b;
+    };
+    int at[kLenClasses];  // next place of each class, first its number of rows
+#pragma unroll
+    for (int k = 0; k < kLenClasses; ++k) at[k] = 0;
+    for (int r0 = 0; r0 < n_b; r0 += 64) {
+      const int c = r0 + lane < n_b ? row_class(r0 + lane) : kLenClasses;
+#pragma unroll
+      for (int k = 0; k < kLenClasses; ++k) at[k] += __popcll(__ballot(c == k));
+    }
+    int full = full_before[j];
+    int next = F + j * n_b - full;  // after the earlier pairs' other rows
+#pragma unroll
+    for (int k = 0; k < kLenClasses; ++k) {
+      const int n = at[k];
+      at[k] = next;
+      next += n;
+    }
+    for (int r0 = 0; r0 < n_b; r0 += 64) {
+      const int r = r0 + lane;
+      const int c = r < n_b ? row_class(r) : kLenClasses;
+      const uint64_t mf = __ballot(c == -1);
+      int pos = full + __popcll(mf & lanes_below);
+      full += __popcll(mf);
+#pragma unroll
+      for (int k = 0; k < kLenClasses; ++k) {
+        const uint64_t m = __ballot(c == k);
+        if (c == k) pos = at[k] + __popcll(m & lanes_below);
+        at[k] += __popcll(m);
+      }
+      if (r < n_b) out[pos] = (pair << 11) | r;
     }
   }
 }
@@ -175,7 +181,6 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
                         uint16_t* __restrict__ o, float* __restrict__ lse,
                         const int32_t* __restrict__ kv_idx,
                         const int32_t* __restrict__ kv_cnt,
-                        const int32_t* __restrict__ order,
                         const int32_t* __restrict__ sched, int* __restrict__ claim, int P,
                         int L, int n_b, float c, const int32_t* __restrict__ rows,
                         int n_rows, int H, int n_split, float* __restrict__ part, int Lq) {
@@ -198,17 +203,17 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
   const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, n = lane & 31;
 
-  // Workgroup w runs on XCD w % 8.  Block lists with a pair count that is a
-  // multiple of 8: the workgroups are persistent, and those of XCD x take
-  // rows from x's launch list (its pairs' full rows, then its pairs one at a
-  // time, so that a pair's K/V blocks are shared through one L2) by an atomic
-  // counter per XCD; once that list is used up they take rows from the other
-  // XCDs' lists, which evens out XCDs that run at different speeds.  Each row
-  // is computed the same way whichever workgroup takes it.  Otherwise there
-  // is one workgroup per row (dense rows: XCD-major over pairs).
-  const bool persistent = !GATHER && (P & 7) == 0;
-  const int per_xcd = (P >> 3) * n_b;  // rows in each XCD's list (persistent form)
-  const int xcd = blockIdx.x & 7;
+  // Workgroup w runs on XCD w % 8.  Block lists with a launch schedule: the
+  // workgroups are persistent, and those of XCD x take rows from x's launch
+  // list (its pairs' full rows, then its pairs one at a time, so that a pair's
+  // K/V blocks are shared through one L2) by an atomic counter per XCD; once
+  // that list is used up they take rows from the other XCDs' lists, which
+  // evens out XCDs that run at different speeds or own fewer pairs (an XCD
+  // without a pair of its own starts at list x % P).  Each row is computed the
+  // same way whichever workgroup takes it.  Otherwise there is one workgroup
+  // per row (dense rows: XCD-major over pairs).
+  const bool persistent = !GATHER && sched != nullptr;
+  const int xcd = P < kXcds ? (blockIdx.x & 7) % P : blockIdx.x & 7;
   int exhausted = 0;                   // lists found empty (thread 0)
   for (int item_iter = 0;; ++item_iter) {
   const int n_qr = GATHER ? ceil_div(n_rows, BLOCK) : n_b;  // query blocks per pair
@@ -220,9 +225,10 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
       for (int k = 0; k < 8 && item < 0; ++k) {
         const int xq = (xcd + k) & 7;
         if (exhausted & (1 << xq)) continue;
-        const int i = atomicAdd(claim + 64 * xq, 1);
-        if (i < per_xcd)
-          item = xq * per_xcd + i;
+        const int rows_x = xcd_pairs(P, xq) * n_b;  // 0 for an XCD without pairs
+        const int i = rows_x > 0 ? atomicAdd(claim + 64 * xq, 1) : 0;
+        if (i < rows_x)
+          item = xcd_first(P, xq) * n_b + i;
         else
           exhausted |= 1 << xq;
       }
@@ -255,7 +261,7 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
     kb0 = n_b * split / n_split;
     cnt = n_b * (split + 1) / n_split - kb0;
   } else {
-    if (!persistent) r = order[row_base + rank];
+    if (!persistent) r = rank;
     cnt = kv_cnt[row_base + r];
     cnt = cnt < 0 ? 0 : (cnt > n_b ? n_b : cnt);
     idx = kv_idx + (row_base + r) * n_b;
@@ -1042,36 +1048,33 @@ void launch_sparse_attention_bf16(const uint16_t* q, const uint16_t* k,
   const int n_b = ceil_div(L, block);
   const int P = B * H;
   const AttnWs lay = attn_ws_layout(B, H, n_b, d, block);
-  int32_t* order = reinterpret_cast<int32_t*>(ws + lay.order);
-  int32_t* sched = reinterpret_cast<int32_t*>(ws + lay.sched);
-  int* claim = reinterpret_cast<int*>(ws + lay.claim);
+  int32_t* sched = nullptr;
+  int* claim = nullptr;
   const float c = scale * kLog2e;
-  hipLaunchKernelGGL(order_rows_kernel, dim3(P, ceil_div(n_b, kOrderRows)), dim3(kOrderRows), 0,
-                     s, kv_cnt, order, n_b);
-  // pair count a multiple of 8: persistent workgroups, as many as the chip
-  // holds at once (2 per CU, 32 CUs per XCD) and no more than the rows
-  dim3 grid(P * n_b);
-  if ((P & 7) == 0) {
-    hipLaunchKernelGGL(schedule_rows_kernel, dim3(8), dim3(1024), 0, s, kv_cnt, order, sched,
-                       claim, P, n_b);
-    grid = dim3(8 * std::min((P >> 3) * n_b, 2 * kCusPerXcd));
+  // Workgroups that the chip holds at once: 256 CUs with two of 4 waves (256
+  // VGPRs a wave), or of 2 waves two (d = 128: 68 KB of LDS each) or four.
+  const int slots = kXcds * kCusPerXcd * (block == 64 && d == 64 ? 4 : 2);
+  // Rows that all run at once need no schedule.
+  if (static_cast<long>(P) * n_b > slots) {
+    sched = reinterpret_cast<int32_t*>(ws + lay.sched);
+    claim = reinterpret_cast<int*>(ws + lay.claim);
+    hipLaunchKernelGGL(schedule_rows_kernel, dim3(kXcds), dim3(1024), 0, s, kv_cnt, sched, claim, P,
+                       n_b);
   }
+  const dim3 grid(sched != nullptr ? slots : P * n_b);
+#define SA_ATTN(DV, BV)                                                                          \
+  hipLaunchKernelGGL((sparse_attn_bf16_kernel<DV, BV, false>), grid, dim3(2 * BV), 0, s, q, k, v, \
+                     o, lse, kv_idx, kv_cnt, sched, claim, P, L, n_b, c, nullptr, 0, H, 1,       \
+                     nullptr, L)
   if (d == 128 && block == 128)
-    hipLaunchKernelGGL((sparse_attn_bf16_kernel<128, 128, false>), grid, dim3(256), 0, s,
-                       q, k, v, o, lse, kv_idx, kv_cnt, order, sched, claim, P, L, n_b, c, nullptr, 0, H, 1,
-                       nullptr, L);
-  else if (d == 128 && block == 64)
-    hipLaunchKernelGGL((sparse_attn_bf16_kernel<128, 64, false>), grid, dim3(128), 0, s,
-                       q, k, v, o, lse, kv_idx, kv_cnt, order, sched, claim, P, L, n_b, c, nullptr, 0, H, 1,
-                       nullptr, L);
-  else if (d == 64 && block == 128)
-    hipLaunchKernelGGL((sparse_attn_bf16_kernel<64, 128, false>), grid, dim3(256), 0, s,
-                       q, k, v, o, lse, kv_idx, kv_cnt, order, sched, claim, P, L, n_b, c, nullptr, 0, H, 1,
-                       nullptr, L);
+    SA_ATTN(128, 128);
+  else if (d == 128)
+    SA_ATTN(128, 64);
+  else if (block == 128)
+    SA_ATTN(64, 128);
   else
-    hipLaunchKernelGGL((sparse_attn_bf16_kernel<64, 64, false>), grid, dim3(128), 0, s,
-                       q, k, v, o, lse, kv_idx, kv_cnt, order, sched, claim, P, L, n_b, c, nullptr, 0, H, 1,
-                       nullptr, L);
+    SA_ATTN(64, 64);
+#undef SA_ATTN
 }
 
 void launch_sparse_attention_f32(const float* q, const float* k,
@@ -1107,11 +1110,11 @@ void launch_gather_attention_bf16(const uint16_t* q, const uint16_t* k, const ui
   const dim3 grid(P * ceil_div(n_rows, kTokRowBlock) * ns);
   if (d == 128)
     hipLaunchKernelGGL((sparse_attn_bf16_kernel<128, kTokRowBlock, true>), grid, dim3(256), 0,
-                       s, q, k, v, o, lse, nullptr, nullptr, nullptr, nullptr, nullptr, P, Lk, n_b, c, rows,
+                       s, q, k, v, o, lse, nullptr, nullptr, nullptr, nullptr, P, Lk, n_b, c, rows,
                        n_rows, H, ns, part, Lq);
   else
     hipLaunchKernelGGL((sparse_attn_bf16_kernel<64, kTokRowBlock, true>), grid, dim3(256), 0,
-                       s, q, k, v, o, lse, nullptr, nullptr, nullptr, nullptr, nullptr, P, Lk, n_b, c, rows,
+                       s, q, k, v, o, lse, nullptr, nullptr, nullptr, nullptr, P, Lk, n_b, c, rows,
                        n_rows, H, ns, part, Lq);
   if (ns > 1) {
     const size_t threads = static_cast<size_t>(P) * n_rows * (d / 4);
