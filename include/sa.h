@@ -284,7 +284,13 @@ int sa_build_block_mask_pooled(const double* qbar, const double* kbar, int B,
  *   kv_idx     [B,H,n_b,n_b] i32; entries outside [0,n_b) are ignored
  *   kv_cnt     [B,H,n_b] i32, clamped to [0,n_b]; a row with no valid entry
  *              outputs zeros and lse = -inf
- *   ws         workspace of at least sa_workspace_size(SA_CALL_SPARSE_ATTENTION)
+ *   ws         workspace of sa_workspace_size(SA_CALL_SPARSE_ATTENTION) bytes.
+ *              bf16 calls of few rows (n_b >= 64, at most four rows per
+ *              workgroup slot of the chip) may cut the lists of their rows
+ *              into equal runs and merge the partial rows (f32) in run order;
+ *              the size has room for that.  A workspace below it but of at
+ *              least 2 * (4 * B*H*n_b rounded up to 256) + 2048 bytes is
+ *              accepted too, and every row is then computed in one piece.
  */
 int sa_sparse_attention(const void* q, const void* k, const void* v, void* o,
                         float* lse, int B, int H, int L, int d, int dtype,
@@ -299,10 +305,11 @@ int sa_sparse_attention(const void* q, const void* k, const void* v, void* o,
  * that forbid hipMalloc).
  *
  * Arguments, results and errors are those of sa_sparse_attention; the same
- * kernels run, so the outputs are bitwise those of sa_sparse_attention.  The
- * scratch (the launch order and schedule of the query blocks, two arrays of
- * B*H*n_b int32, and 8 row counters) lives in a 4 MiB array that the library
- * holds on each device it runs on until the process ends, so
+ * kernels run, so the outputs are bitwise those of sa_sparse_attention with a
+ * workspace of sa_workspace_size bytes.  The scratch lives in a 70 MiB array
+ * that the library holds on each device it runs on until the process ends.
+ * 4 MiB of it bound the size of a call (the launch order and schedule of the
+ * query blocks, two arrays of B*H*n_b int32, and 8 row counters):
  * B*H*n_b <= 524032; larger sizes fail with
  * SA_ERR_UNSUPPORTED before any launch.  Every element of the scratch that a
  * call reads is written by that call first (the row counters are set to zero
@@ -413,7 +420,8 @@ int sa_cache_indicator(const void* y_v, const void* y_v_hat,
                        void* stream);
 
 /*
- * Minimum workspace bytes of a call (SA_CALL_*) at the given sizes; L_a is
+ * Workspace bytes of a call (SA_CALL_*) at the given sizes (the least it
+ * accepts, but for SA_CALL_SPARSE_ATTENTION, see there); L_a is
  * read by SA_CALL_CROSS_SCORES and SA_CALL_CACHE_INDICATOR (0 = no audio),
  * and SA_CALL_CACHE_INDICATOR reads B, L_v and L_a only.
  * SA_CALL_TOKEN_ATTENTION reads B, H, L_v (the sequence length L), d and

@@ -13,9 +13,12 @@
 #include "sa_internal.h"
 
 // Scratch of sa_sparse_attention_noalloc: each device holds its own copy of
-// this array until the process ends.  Calls on one device share it.
+// this array until the process ends.  Calls on one device share it.  Behind
+// the launch lists (AttnWs::min, which bounds what the call accepts) there is
+// room for the runs of any split_rows call (AttnWs::starts and part).
 constexpr size_t kStaticScratchBytes = static_cast<size_t>(4) << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+constexpr size_t kStaticSplitBytes = static_cast<size_t>(66) << 20;
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticSplitBytes];
 
 namespace {
 
@@ -124,13 +127,16 @@ int check_sparse_attention_args(const char* fn, const void* q, const void* k, co
 void launch_sparse_attention(const void* q, const void* k, const void* v, void* o, float* lse,
                              int B, int H, int L, int d, int dtype, float scale, int block,
                              const int32_t* kv_idx, const int32_t* kv_cnt, char* ws,
-                             hipStream_t s) {
-  if (dtype == SA_BF16)
-    sa::launch_sparse_attention_bf16(
+                             size_t ws_bytes, hipStream_t s) {
+  const sa::AttnWs lay = sa::attn_ws_layout(B, H, sa::ceil_div(L, block), d, block);
+  if (dtype == SA_BF16) {
+    const bool split = lay.total > lay.min && ws_bytes >= lay.total &&
+                       &sa::launch_sparse_attention_split_bf16 != nullptr;
+    (split ? sa::launch_sparse_attention_split_bf16 : sa::launch_sparse_attention_bf16)(
         static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
         static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), lse, B, H, L, d,
         scale, block, kv_idx, kv_cnt, ws, s);
-  else
+  } else
     sa::launch_sparse_attention_f32(
         static_cast<const float*>(q), static_cast<const float*>(k),
         static_cast<const float*>(v), static_cast<float*>(o), lse, B, H, L, d, scale,
@@ -442,9 +448,9 @@ int sa_sparse_attention(const void* q, const void* k, const void* v, void* o, fl
   SA_TRY(check_sparse_attention_args(fn, q, k, v, o, lse, B, H, L, d, dtype, scale, block,
                                      kv_idx, kv_cnt));
   const int n_b = sa::ceil_div(L, block);
-  SA_TRY(check_ws(fn, ws, ws_bytes, sa::attn_ws_layout(B, H, n_b, d, block).total));
+  SA_TRY(check_ws(fn, ws, ws_bytes, sa::attn_ws_layout(B, H, n_b, d, block).min));
   launch_sparse_attention(q, k, v, o, lse, B, H, L, d, dtype, scale, block, kv_idx, kv_cnt,
-                          static_cast<char*>(ws), static_cast<hipStream_t>(stream));
+                          static_cast<char*>(ws), ws_bytes, static_cast<hipStream_t>(stream));
   return check_launch(fn);
 }
 
@@ -456,7 +462,7 @@ int sa_sparse_attention_noalloc(const void* q, const void* k, const void* v, voi
   SA_TRY(check_sparse_attention_args(fn, q, k, v, o, lse, B, H, L, d, dtype, scale, block,
                                      kv_idx, kv_cnt));
   const int n_b = sa::ceil_div(L, block);
-  const size_t need = sa::attn_ws_layout(B, H, n_b, d, block).total;
+  const size_t need = sa::attn_ws_layout(B, H, n_b, d, block).min;
   if (need > kStaticScratchBytes)
     return fail(SA_ERR_UNSUPPORTED,
                 "%s: B=%d H=%d n_b=%d needs %zu bytes of scratch, above the %zu bytes the "
@@ -466,7 +472,7 @@ int sa_sparse_attention_noalloc(const void* q, const void* k, const void* v, voi
   char* ws = nullptr;
   SA_TRY(static_scratch(fn, s, &ws));
   launch_sparse_attention(q, k, v, o, lse, B, H, L, d, dtype, scale, block, kv_idx, kv_cnt,
-                          ws, s);
+                          ws, sizeof(scratch), s);
   return check_launch(fn);
 }
 

@@ -24,7 +24,8 @@
 // XCD takes every 8th (batch, head) pair, first the full rows of all its pairs
 // (protected rows hold the full list), then the other rows one pair at a time,
 // so that a pair's K/V blocks are shared through one XCD's L2 and the long full
-// rows do not run alone at the end of the launch.
+// rows do not run alone at the end of the launch.  Calls of few rows may cut
+// the rows' lists into equal runs instead, and merge the rows that runs share.
 //
 // Gather form: dense rows gathered by index (protected tokens) or all rows
 // of a query tensor of another length (cross-modal attention), every key
@@ -42,7 +43,6 @@ namespace sa {
 namespace {
 
 constexpr int kTile = 64;       // keys per LDS tile
-constexpr int kCusPerXcd = 32;  // MI355X: 8 XCDs of 32 CUs
 
 // Launch schedule.  Workgroup w runs on XCD w % 8, which owns the pairs x,
 // x+8, x+16, ... (b,h); entry i of XCD x's list (pair << 11 | query block) is
@@ -58,7 +58,6 @@ constexpr int kCusPerXcd = 32;  // MI355X: 8 XCDs of 32 CUs
 // barriers in all).  Ranking every row exactly in a kernel of its own first
 // and writing the lists in a second took 5 + 6 us at P = 24, n_b = 256; this
 // one takes about 6.
-constexpr int kXcds = 8;
 constexpr int kLenClasses = 8;
 __host__ __device__ constexpr int xcd_pairs(int P, int x) { return (P - x + kXcds - 1) / kXcds; }
 // Pairs of the XCDs before x: their lists come first in `sched`.
@@ -67,10 +66,83 @@ __host__ __device__ constexpr int xcd_first(int P, int x) {
   return x * q + (x < rem ? x : rem);
 }
 
+//
+// Calls of few rows (split_rows) have one workgroup more, which lays the rows'
+// lists end to end, pair by pair, and cuts them into one equal run per
+// workgroup slot, so that a slot may begin and end inside a list: `starts` gets
+// (row, list entry) of every run's first entry; run c ends where run c + 1
+// starts, the last at row R, entry 0.  A row costs kRowCost entries besides its
+// own (list, Q rows, pipeline fill, epilogue: about 15 k cycles against 5.7 k
+// an entry of 128 keys), a run has at least kMinRun of them, and a cut within
+// kSnap entries of a list's end moves to that end.  starts[slots + 1].x says
+// whether the runs are to be used.  Whole rows claimed one at a time end with
+// the longest one, at 0.72 of an entry's usual time once it has the CU to
+// itself, or about a quarter of a row after the mean; runs are equal but
+// static, and end up to 10 % late on the slowest XCD, so they are used from
+// that line on.  At d 128, block 128, n_b 256, a quarter of the pairs kept and
+// 5 % of the rows full: 466 -> 209 us with one head (0.5 rows a slot), 647 ->
+// 473 with three, 717 -> 619 with four (max list / run 1.7), but 874 -> 907
+// with six (1.16) and 1106 -> 1202 with eight, where whole rows stay.
+constexpr int kRowCost = 2;
+constexpr int kMinRun = 16;
+constexpr int kSnap = 4;
+__device__ void cut_rows(const int32_t* __restrict__ kv_cnt, int2* __restrict__ starts, int slots,
+                         int R, int n_b) {
+  __shared__ int wave_tot[1024 / 64], wave_max[1024 / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int K = ceil_div(R, 1024);  // rows per thread
+  const int r0 = min(tid * K, R), r1 = min(r0 + K, R);
+  auto row_cnt = [&](int r) { return min(max(kv_cnt[r], 0), n_b); };
+  int own = 0, longest = 0;
+  for (int r = r0; r < r1; ++r) {
+    const int w = row_cnt(r) + kRowCost;
+    own += w;
+    longest = max(longest, w);
+  }
+  int incl = own;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += u;
+    longest = max(longest, __shfl_xor(longest, o, 64));
+  }
+  if (lane == 63) {
+    wave_tot[wave] = incl;
+    wave_max[wave] = longest;
+  }
+  __syncthreads();
+  int before = incl - own, total = 0;
+#pragma unroll
+  for (int w = 0; w < 1024 / 64; ++w) {
+    if (w < wave) before += wave_tot[w];
+    total += wave_tot[w];
+    longest = max(longest, wave_max[w]);
+  }
+  const int run = max(ceil_div(total, slots), kMinRun);
+  if (tid == 0) {
+    const float whole = fmaxf(0.72f * longest, static_cast<float>(run) + 0.25f * total / R);
+    starts[slots + 1] = make_int2(whole > 1.1f * run ? 1 : 0, 0);
+  }
+  for (int r = r0; r < r1; ++r) {
+    const int cnt = row_cnt(r);
+    // cuts c * run in [before, before + cnt + kRowCost)
+    for (int c = ceil_div(before, run); c * run < before + cnt + kRowCost; ++c) {
+      const int e = c * run - before - kRowCost;
+      starts[c] = e < kSnap ? make_int2(r, 0) : cnt - e < kSnap ? make_int2(r + 1, 0) : make_int2(r, e);
+    }
+    before += cnt + kRowCost;
+  }
+  for (int c = ceil_div(total, run) + tid; c <= slots; c += 1024) starts[c] = make_int2(R, 0);
+}
+
 __global__ void __launch_bounds__(1024)
 schedule_rows_kernel(const int32_t* __restrict__ kv_cnt, int32_t* __restrict__ sched,
-                     int* __restrict__ claim, int P, int n_b) {
+                     int* __restrict__ claim, int P, int n_b, int2* __restrict__ starts, int slots) {
   __shared__ int full_before[kMaxPairs / kXcds + 2];  // full rows of the list's earlier pairs
+  if (blockIdx.x == kXcds) {
+    cut_rows(kv_cnt, starts, slots, P * n_b, n_b);
+    return;
+  }
   const int x = blockIdx.x, np = xcd_pairs(P, x), tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   constexpr int NW = 1024 / 64;
@@ -173,7 +245,14 @@ __device__ __forceinline__ float max_halves(float x) {
 // per workgroup: with n_split == 1 the workgroup keeps every key and writes
 // O and lse to the query's own row; otherwise it writes its unnormalised O,
 // running max m (log2 units) and row sum to `part` for token_combine_kernel.
-template <int D, int BLOCK, bool GATHER>
+// SPLIT: if the schedule says so, run c of `starts` per workgroup (otherwise
+// whole rows by `sched` as above); a row that the run
+// holds whole is written to O and lse, and of a row that it shares with other
+// runs the part of the list that it holds goes to partial 2c (the run starts
+// inside the list) or 2c + 1 (it starts at the list's start) for
+// row_combine_kernel.
+enum class Rows { kList, kGather, kSplit };
+template <int D, int BLOCK, Rows ROWS>
 __global__ void __launch_bounds__(BLOCK * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
 sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
                         const uint16_t* __restrict__ k,
@@ -183,7 +262,10 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
                         const int32_t* __restrict__ kv_cnt,
                         const int32_t* __restrict__ sched, int* __restrict__ claim, int P,
                         int L, int n_b, float c, const int32_t* __restrict__ rows,
-                        int n_rows, int H, int n_split, float* __restrict__ part, int Lq) {
+                        int n_rows, int H, int n_split, float* __restrict__ part, int Lq,
+                        const int2* __restrict__ starts) {
+  constexpr bool GATHER = ROWS == Rows::kGather;
+  constexpr bool SPLIT = ROWS == Rows::kSplit;
   constexpr int NW = BLOCK / 32;             // waves per workgroup
   constexpr int TPB = BLOCK / kTile;         // tiles per key block
   constexpr int KC = D / 16;                 // k-steps of Q K^T
@@ -212,14 +294,31 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
   // without a pair of its own starts at list x % P).  Each row is computed the
   // same way whichever workgroup takes it.  Otherwise there is one workgroup
   // per row (dense rows: XCD-major over pairs).
-  const bool persistent = !GATHER && sched != nullptr;
+  const bool runs =
+      SPLIT && __builtin_amdgcn_readfirstlane(starts[static_cast<int>(gridDim.x) + 1].x) != 0;
+  const bool persistent = !GATHER && !runs && sched != nullptr;
   const int xcd = P < kXcds ? (blockIdx.x & 7) % P : blockIdx.x & 7;
   int exhausted = 0;                   // lists found empty (thread 0)
+  // SPLIT: consecutive runs on one XCD, so that a pair's K/V blocks are shared
+  // through its L2
+  int run = 0, split_row = 0, split_i = 0;
+  int2 run_end = make_int2(0, 0);
+  if (runs) {
+    run = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    split_row = __builtin_amdgcn_readfirstlane(starts[run].x);
+    split_i = __builtin_amdgcn_readfirstlane(starts[run].y);
+    run_end.x = __builtin_amdgcn_readfirstlane(starts[run + 1].x);
+    run_end.y = __builtin_amdgcn_readfirstlane(starts[run + 1].y);
+  }
   for (int item_iter = 0;; ++item_iter) {
   const int n_qr = GATHER ? ceil_div(n_rows, BLOCK) : n_b;  // query blocks per pair
   const int n_q = GATHER ? n_qr * n_split : n_b;              // workgroups per pair
   int pair, rank = 0, r = 0;
-  if (persistent) {
+  if (runs) {
+    if (split_row > run_end.x || (split_row == run_end.x && split_i >= run_end.y)) break;
+    pair = split_row / n_b;
+    r = split_row - pair * n_b;
+  } else if (persistent) {
     if (tid == 0) {
       int item = -1;
       for (int k = 0; k < 8 && item < 0; ++k) {
@@ -253,6 +352,7 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
   }
   const size_t row_base = static_cast<size_t>(pair) * n_b;
   int cnt, kb0 = 0, split = 0;
+  bool partial = false;  // SPLIT: the run holds a part of the row's list
   const int32_t* idx = nullptr;
   if constexpr (GATHER) {
     // consecutive ranks share a key run and so its K/V tiles in L2
@@ -261,10 +361,16 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
     kb0 = n_b * split / n_split;
     cnt = n_b * (split + 1) / n_split - kb0;
   } else {
-    if (!persistent) r = rank;
+    if (!persistent && !runs) r = rank;
     cnt = kv_cnt[row_base + r];
     cnt = cnt < 0 ? 0 : (cnt > n_b ? n_b : cnt);
     idx = kv_idx + (row_base + r) * n_b;
+    if (runs) {  // entries [split_i, last) of the list
+      const int last = split_row == run_end.x ? min(run_end.y, cnt) : cnt;
+      partial = split_i > 0 || last < cnt;
+      idx += split_i;
+      cnt = last - split_i;
+    }
   }
 
   // Compact the list into 64-key tiles (wave 0): entries outside [0, n_b)
@@ -706,6 +812,27 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
       return;
     }
   }
+  if (runs) {
+    const int id = 2 * run + (split_i > 0 ? 0 : 1);
+    split_i = 0;
+    ++split_row;
+    if (partial) {
+      const size_t prow = static_cast<size_t>(id) * BLOCK + (tid >> 6) * 32 + n;
+      float* orow = part + prow * D;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {
+          const f32x4 val = {acc[dt][4 * rg], acc[dt][4 * rg + 1], acc[dt][4 * rg + 2],
+                             acc[dt][4 * rg + 3]};
+          *reinterpret_cast<f32x4*>(orow + 32 * dt + 8 * rg + 4 * g) = val;
+        }
+      if (g == 0)
+        reinterpret_cast<float2*>(part + 2 * static_cast<size_t>(gridDim.x) * BLOCK * D)[prow] =
+            make_float2(m, ltot);
+      continue;
+    }
+  }
   const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
   if (qvalid) {
     uint16_t* orow = o + (static_cast<size_t>(pair) * LQ + qrow) * D;
@@ -767,6 +894,55 @@ token_combine_kernel(const float* __restrict__ part, int n_split, int P, int Lq,
   *reinterpret_cast<u32x2*>(o + (static_cast<size_t>(pair) * Lq + t) * D + d4) = val;
   if (lse != nullptr && d4 == 0)
     lse[static_cast<size_t>(pair) * Lq + t] = den > 0.f ? (M + __log2f(den)) * kLn2 : -INFINITY;
+}
+
+// The rows that several runs share: workgroup c merges the row whose first part
+// run c holds (if there is one), in run order, as token_combine_kernel does.
+constexpr int kRowCombThreads = 256;
+template <int D, int BLOCK>
+__global__ void __launch_bounds__(kRowCombThreads)
+row_combine_kernel(const float* __restrict__ part, const int2* __restrict__ starts, int n_b, int L,
+                   uint16_t* __restrict__ o, float* __restrict__ lse) {
+  const int c = blockIdx.x, runs = gridDim.x;
+  if (starts[runs + 1].x == 0) return;
+  const int2 cut = starts[c + 1], from = starts[c];
+  if (cut.y == 0 || (from.x == cut.x && from.y > 0)) return;  // no shared row begins in run c
+  int n = 2;  // parts: run c's second partial, then the first ones of runs c + 1, ...
+  while (c + n <= runs && starts[c + n].x == cut.x && starts[c + n].y > 0) ++n;
+  const float2* ml = reinterpret_cast<const float2*>(part + 2 * static_cast<size_t>(runs) * BLOCK * D);
+  const int pair = cut.x / n_b, row0 = (cut.x - pair * n_b) * BLOCK;
+  constexpr int TPR = D / 4;
+#pragma unroll 4
+  for (int u = 0; u < BLOCK * TPR / kRowCombThreads; ++u) {
+    const int t = u * kRowCombThreads + static_cast<int>(threadIdx.x);
+    const int j = t / TPR, d4 = (t % TPR) * 4;
+    if (row0 + j >= L) continue;
+    auto prow = [&](int s) {
+      return static_cast<size_t>(s == 0 ? 2 * c + 1 : 2 * (c + s)) * BLOCK + j;
+    };
+    float M = -INFINITY;
+    for (int s = 0; s < n; ++s) {
+      const float2 v = ml[prow(s)];
+      if (v.y > 0.f) M = fmaxf(M, v.x);
+    }
+    float den = 0.f;
+    f32x4 num = {0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < n; ++s) {
+      const float2 v = ml[prow(s)];
+      const float w = v.y > 0.f ? exp2f(v.x - M) : 0.f;
+      const f32x4 x = ldg_f32x4(part + prow(s) * D + d4);
+      den = fmaf(w, v.y, den);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) num[e] = fmaf(w, x[e], num[e]);
+    }
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    const u32x2 val = {pack_bf16x2(num[0] * inv, num[1] * inv),
+                       pack_bf16x2(num[2] * inv, num[3] * inv)};
+    const size_t orow = static_cast<size_t>(pair) * L + row0 + j;
+    *reinterpret_cast<u32x2*>(o + orow * D + d4) = val;
+    if (lse != nullptr && d4 == 0)
+      lse[orow] = den > 0.f ? (M + __log2f(den)) * kLn2 : -INFINITY;
+  }
 }
 
 // ---- fp32 path ------------------------------------------------------------
@@ -1039,33 +1215,51 @@ sparse_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 
 }  // namespace
 
-void launch_sparse_attention_bf16(const uint16_t* q, const uint16_t* k,
-                                  const uint16_t* v, uint16_t* o, float* lse,
-                                  int B, int H, int L, int d, float scale,
-                                  int block, const int32_t* kv_idx,
-                                  const int32_t* kv_cnt, char* ws,
-                                  hipStream_t s) {
-  const int n_b = ceil_div(L, block);
-  const int P = B * H;
-  const AttnWs lay = attn_ws_layout(B, H, n_b, d, block);
+template <int D, int BLOCK>
+static void sparse_attention_bf16(const uint16_t* q, const uint16_t* k, const uint16_t* v,
+                                  uint16_t* o, float* lse, int B, int H, int L, float scale,
+                                  const int32_t* kv_idx, const int32_t* kv_cnt, char* ws,
+                                  bool split, hipStream_t s) {
+  const int n_b = ceil_div(L, BLOCK), P = B * H;
+  const AttnWs lay = attn_ws_layout(B, H, n_b, D, BLOCK);
+  const float c = scale * kLog2e;
+  const int slots = attn_slots(D, BLOCK);
+  const int rows = P * n_b;
+  if (split) {
+    int2* starts = reinterpret_cast<int2*>(ws + lay.starts);
+    float* part = reinterpret_cast<float*>(ws + lay.part);
+    int32_t* sched = reinterpret_cast<int32_t*>(ws + lay.sched);
+    int* claim = reinterpret_cast<int*>(ws + lay.claim);
+    hipLaunchKernelGGL(schedule_rows_kernel, dim3(kXcds + 1), dim3(1024), 0, s, kv_cnt, sched,
+                       claim, P, n_b, starts, slots);
+    hipLaunchKernelGGL((sparse_attn_bf16_kernel<D, BLOCK, Rows::kSplit>), dim3(slots),
+                       dim3(2 * BLOCK), 0, s, q, k, v, o, lse, kv_idx, kv_cnt, sched, claim, P, L,
+                       n_b, c, nullptr, 0, H, 1, part, L, starts);
+    hipLaunchKernelGGL((row_combine_kernel<D, BLOCK>), dim3(slots), dim3(kRowCombThreads), 0, s,
+                       part, starts, n_b, L, o, lse);
+    return;
+  }
   int32_t* sched = nullptr;
   int* claim = nullptr;
-  const float c = scale * kLog2e;
-  // Workgroups that the chip holds at once: 256 CUs with two of 4 waves (256
-  // VGPRs a wave), or of 2 waves two (d = 128: 68 KB of LDS each) or four.
-  const int slots = kXcds * kCusPerXcd * (block == 64 && d == 64 ? 4 : 2);
   // Rows that all run at once need no schedule.
-  if (static_cast<long>(P) * n_b > slots) {
+  if (rows > slots) {
     sched = reinterpret_cast<int32_t*>(ws + lay.sched);
     claim = reinterpret_cast<int*>(ws + lay.claim);
     hipLaunchKernelGGL(schedule_rows_kernel, dim3(kXcds), dim3(1024), 0, s, kv_cnt, sched, claim, P,
-                       n_b);
+                       n_b, nullptr, 0);
   }
-  const dim3 grid(sched != nullptr ? slots : P * n_b);
-#define SA_ATTN(DV, BV)                                                                          \
-  hipLaunchKernelGGL((sparse_attn_bf16_kernel<DV, BV, false>), grid, dim3(2 * BV), 0, s, q, k, v, \
-                     o, lse, kv_idx, kv_cnt, sched, claim, P, L, n_b, c, nullptr, 0, H, 1,       \
-                     nullptr, L)
+  hipLaunchKernelGGL((sparse_attn_bf16_kernel<D, BLOCK, Rows::kList>),
+                     dim3(sched != nullptr ? slots : rows), dim3(2 * BLOCK), 0, s, q, k, v, o, lse,
+                     kv_idx, kv_cnt, sched, claim, P, L, n_b, c, nullptr, 0, H, 1, nullptr, L,
+                     nullptr);
+}
+
+static void sparse_attention_bf16(const uint16_t* q, const uint16_t* k, const uint16_t* v,
+                                  uint16_t* o, float* lse, int B, int H, int L, int d, float scale,
+                                  int block, const int32_t* kv_idx, const int32_t* kv_cnt, char* ws,
+                                  bool split, hipStream_t s) {
+#define SA_ATTN(DV, BV)                                                                    \
+  sparse_attention_bf16<DV, BV>(q, k, v, o, lse, B, H, L, scale, kv_idx, kv_cnt, ws, split, s)
   if (d == 128 && block == 128)
     SA_ATTN(128, 128);
   else if (d == 128)
@@ -1075,6 +1269,22 @@ void launch_sparse_attention_bf16(const uint16_t* q, const uint16_t* k,
   else
     SA_ATTN(64, 64);
 #undef SA_ATTN
+}
+
+void launch_sparse_attention_bf16(const uint16_t* q, const uint16_t* k,
+                                  const uint16_t* v, uint16_t* o, float* lse,
+                                  int B, int H, int L, int d, float scale,
+                                  int block, const int32_t* kv_idx,
+                                  const int32_t* kv_cnt, char* ws,
+                                  hipStream_t s) {
+  sparse_attention_bf16(q, k, v, o, lse, B, H, L, d, scale, block, kv_idx, kv_cnt, ws, false, s);
+}
+
+void launch_sparse_attention_split_bf16(const uint16_t* q, const uint16_t* k, const uint16_t* v,
+                                        uint16_t* o, float* lse, int B, int H, int L, int d,
+                                        float scale, int block, const int32_t* kv_idx,
+                                        const int32_t* kv_cnt, char* ws, hipStream_t s) {
+  sparse_attention_bf16(q, k, v, o, lse, B, H, L, d, scale, block, kv_idx, kv_cnt, ws, true, s);
 }
 
 void launch_sparse_attention_f32(const float* q, const float* k,
@@ -1109,13 +1319,13 @@ void launch_gather_attention_bf16(const uint16_t* q, const uint16_t* k, const ui
   float* part = ns > 1 ? reinterpret_cast<float*>(ws) : nullptr;
   const dim3 grid(P * ceil_div(n_rows, kTokRowBlock) * ns);
   if (d == 128)
-    hipLaunchKernelGGL((sparse_attn_bf16_kernel<128, kTokRowBlock, true>), grid, dim3(256), 0,
+    hipLaunchKernelGGL((sparse_attn_bf16_kernel<128, kTokRowBlock, Rows::kGather>), grid, dim3(256), 0,
                        s, q, k, v, o, lse, nullptr, nullptr, nullptr, nullptr, P, Lk, n_b, c, rows,
-                       n_rows, H, ns, part, Lq);
+                       n_rows, H, ns, part, Lq, nullptr);
   else
-    hipLaunchKernelGGL((sparse_attn_bf16_kernel<64, kTokRowBlock, true>), grid, dim3(256), 0,
+    hipLaunchKernelGGL((sparse_attn_bf16_kernel<64, kTokRowBlock, Rows::kGather>), grid, dim3(256), 0,
                        s, q, k, v, o, lse, nullptr, nullptr, nullptr, nullptr, P, Lk, n_b, c, rows,
-                       n_rows, H, ns, part, Lq);
+                       n_rows, H, ns, part, Lq, nullptr);
   if (ns > 1) {
     const size_t threads = static_cast<size_t>(P) * n_rows * (d / 4);
     const dim3 cgrid(static_cast<unsigned>((threads + 255) / 256));

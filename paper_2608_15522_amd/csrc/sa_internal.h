@@ -74,19 +74,47 @@ inline MaskWs mask_ws_layout(int B, int H, int n_b, int d) {
   return w;
 }
 
+constexpr int kXcds = 8, kCusPerXcd = 32;  // MI355X
+
+// bf16 sparse attention: workgroups that the chip holds at once, two of 4 waves
+// (256 VGPRs a wave) a CU, or of 2 waves two (d = 128: 68 KB of LDS each) or
+// four.
+inline int attn_slots(int d, int block) {
+  return kXcds * kCusPerXcd * (block == 64 && d == 64 ? 4 : 2);
+}
+// Whether the lists may be cut into one equal run per slot (the schedule kernel
+// decides, from the lists' lengths): with more than four rows a slot, or lists
+// of less than 64 blocks, whole rows were at least as fast at every density
+// down to 10 %, and the calls are spared the combine launch (about 2 us).
+constexpr int kSplitRounds = 4;
+inline bool split_rows(int P, int n_b, int d, int block) {
+  return n_b >= 64 && static_cast<long long>(P) * n_b <= kSplitRounds * attn_slots(d, block);
+}
+
 struct AttnWs {
   size_t sched;   // int [B*H][n_b]  the XCDs' launch lists, one after the other
   size_t claim;   // int [8][64]  rows taken from each XCD's list (one per 256 bytes)
+  size_t min;     // bytes without the parts below, which a call can do without
+  size_t starts;  // int2 [slots + 2]  first list entry of each run; whether to use them
+  size_t part;    // float [2 slots][block][d], then float2 [2 slots][block]
   size_t total;
 };
 
-// The lists take half of what the size has room for: the size itself is kept,
-// since it also bounds what sa_sparse_attention_noalloc accepts.
-inline AttnWs attn_ws_layout(int B, int H, int n_b, int /*d*/, int /*block*/) {
+// The lists take half of what `min` has room for: that size is kept, since it
+// also bounds what sa_sparse_attention_noalloc accepts.
+inline AttnWs attn_ws_layout(int B, int H, int n_b, int d, int block) {
   AttnWs w{};
   size_t off = 0;
   w.sched = off; off += 2 * align_up(sizeof(int32_t) * B * H * n_b);
   w.claim = off; off += align_up(sizeof(int32_t) * 8 * 64);
+  w.min = off;
+  w.starts = w.part = off;
+  if (split_rows(B * H, n_b, d, block)) {
+    const size_t slots = attn_slots(d, block);
+    off += align_up(8 * (slots + 2));
+    w.part = off;
+    off += align_up(2 * slots * block * (static_cast<size_t>(d) * 4 + 8));
+  }
   w.total = off;
   return w;
 }
@@ -204,6 +232,13 @@ void launch_sparse_attention_bf16(const uint16_t* q, const uint16_t* k,
                                   int block, const int32_t* kv_idx,
                                   const int32_t* kv_cnt, char* ws,
                                   hipStream_t s);
+// The same with the lists cut into one run per slot (split_rows): ws holds
+// attn_ws_layout's total.  Weak: a host-only build of the C ABI links without
+// it and then does not split.
+__attribute__((weak)) void launch_sparse_attention_split_bf16(
+    const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* o, float* lse, int B, int H,
+    int L, int d, float scale, int block, const int32_t* kv_idx, const int32_t* kv_cnt, char* ws,
+    hipStream_t s);
 void launch_sparse_attention_f32(const float* q, const float* k,
                                  const float* v, float* o, float* lse, int B,
                                  int H, int L, int d, float scale, int block,

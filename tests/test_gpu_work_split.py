@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2608_15522_amd as sa
-from sa_parity import SAL_ABS, SAL_REL, TOL_O
+from sa_parity import SAL_ABS, SAL_REL, TOL_LSE, TOL_O
 
 pytestmark = pytest.mark.gpu
 
@@ -112,3 +112,51 @@ def test_sparse_attention_schedule(H, n_b, tail, d, block):
             at = keep[members].nonzero()[:, 0]
             p = torch.softmax(scale * (qd[rows] @ kd[at].T.contiguous()), 1)
             assert (o[0, h, rows].double() - p @ vd[at]).abs().max() <= TOL_O["bf16"], (h, r)
+
+
+# Lists cut into equal runs: the shortest lists that are cut and the most rows,
+# rows held by several runs, runs of several rows, empty and full rows, entries
+# outside the range, a tail block.  Against the same lists in one piece (a
+# workspace without room for the partial rows): O differs by the rounding of P
+# against another running maximum (2^-9 a term, as TOL_O allows) and the lse by
+# that of its bf16 row sum, so both are held to the tolerances against the
+# reference; the entry point without a workspace gives the same bits.
+@pytest.mark.parametrize("H,n_b,tail,d,block,kind", [
+    (1, 64, 64, 128, 64, "full"), (32, 64, 3, 128, 128, "mixed"), (1, 65, 1, 64, 128, "one"),
+    (3, 256, 120, 128, 128, "mixed"), (5, 200, 64, 64, 64, "mixed"), (2, 70, 9, 64, 64, "empty")])
+def test_sparse_attention_runs(H, n_b, tail, d, block, kind):
+    L = (n_b - 1) * block + tail
+    print(f"case runs H={H} n_b={n_b} tail={tail} d={d} block={block} {kind}", flush=True)
+    rng = np.random.default_rng(n_b + H)
+    cnt = {"full": np.full((1, H, n_b), n_b), "empty": np.zeros((1, H, n_b)),
+           "one": np.zeros((1, H, n_b)),
+           "mixed": rng.integers(0, n_b // 4 + 1, (1, H, n_b))}[kind].astype(np.int32)
+    if kind == "one":
+        cnt[0, 0, n_b - 1] = n_b
+    if kind == "mixed":
+        cnt[0, :, rng.integers(0, n_b, n_b // 16)] = n_b
+    idx = np.full((1, H, n_b, n_b), -1, np.int32)
+    for h in range(H):
+        for r in range(n_b):
+            idx[0, h, r, :cnt[0, h, r]] = np.sort(rng.permutation(n_b)[:cnt[0, h, r]])
+    idx[0, 0, n_b // 2, :2] = (-3, n_b)  # ignored
+    idx, cnt = torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda()
+    q, k, v = (_randn(1, H, L, d, seed=i) for i in (1, 2, 3))
+    need = sa.sa_workspace_size(sa.SA_CALL_SPARSE_ATTENTION, 1, H, L, 1, d, block)
+    least = 2 * -(-4 * H * n_b // 256) * 256 + 2048
+    assert need > least
+    out = []
+    for n in (need, least):
+        ws = torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+        out.append(sa.sa_sparse_attention(q, k, v, d**-0.5, block, idx, cnt, want_lse=True, ws=ws))
+    with pytest.raises(sa.binding.SaError):
+        sa.sa_sparse_attention(q, k, v, d**-0.5, block, idx, cnt, ws=ws[:least - 1])
+    (o, lse), (o1, lse1) = out
+    assert (o.float() - o1.float()).abs().max() <= 2 * TOL_O["bf16"]
+    assert torch.equal(torch.isneginf(lse), torch.isneginf(lse1))
+    some = ~torch.isneginf(lse1)
+    if some.any():
+        assert (lse - lse1)[some].abs().max() <= 2 * TOL_LSE["bf16"]
+    o2, lse2 = torch.full_like(o, float("nan")), torch.full_like(lse, float("nan"))
+    sa.sa_sparse_attention_noalloc(q, k, v, d**-0.5, block, idx, cnt, o2, lse2)
+    assert torch.equal(o.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, lse2)
