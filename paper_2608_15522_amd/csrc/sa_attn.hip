@@ -277,7 +277,7 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
 
   __shared__ __attribute__((aligned(1024))) uint16_t Ks[2][TILE_ELEMS];
   __shared__ __attribute__((aligned(1024))) uint16_t Vs[2][TILE_ELEMS];
-  __shared__ uint16_t tiles[kMaxBlocks * TPB];  // valid tiles, as key0 / 64
+  __shared__ uint16_t tiles[GATHER ? 1 : kMaxBlocks * TPB];  // valid tiles, as key0 / 64
   __shared__ int ntiles_sh, nfull_sh, item_sh;
 
   const int tid = threadIdx.x;
@@ -377,13 +377,16 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
   // are dropped, and so is the second half of a last block of <= 64 keys.
   // Full tiles keep the list order; the tile that reaches past L (at most
   // one per list entry of block n_b-1) is placed after all of them, so that
-  // only the last iterations mask keys.
-  if (tid < 64) {
+  // only the last iterations mask keys.  GATHER: the tiles of the run in order,
+  // without a list; with that and the 16-byte stores of O the two cross-modal
+  // forwards and the saliency at H24 L_v32760 L_a512 take 751 instead of 777
+  // us (8 tiles a row there, so that what surrounds the loop weighs most).
+  if (!GATHER && tid < 64) {
     int nfull = 0, npart = 0;
     const uint64_t below = (1ull << lane) - 1ull;
     for (int i0 = 0; i0 < cnt; i0 += 64) {
       const int i = i0 + lane;
-      const int kb = i < cnt ? (GATHER ? kb0 + i : idx[i]) : -1;
+      const int kb = i < cnt ? idx[i] : -1;
       const bool v0 = kb >= 0 && kb < n_b;
       const bool v1 = TPB == 2 && v0 && kb * BLOCK + kTile < L;
       const bool f0 = v0 && kb * BLOCK + kTile <= L;
@@ -451,10 +454,12 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
   const int v_off1 = (8 + tr_key) * 64 + 16 * ((tr_byte >> 4) ^ plane_swz(8 + tr_key)) +
                      (tr_byte & 15);
 
-  __syncthreads();  // the tile list is visible
-  const int T = ntiles_sh;
-  const int T_full = nfull_sh;
+  if constexpr (!GATHER) __syncthreads();  // the tile list is visible
+  const int run_keys = min((kb0 + cnt) * BLOCK, L) - kb0 * BLOCK;  // GATHER
+  const int T = GATHER ? ceil_div(run_keys, kTile) : ntiles_sh;
+  const int T_full = GATHER ? run_keys / kTile : nfull_sh;
   auto tile_key0 = [&](int t) {
+    if constexpr (GATHER) return kb0 * BLOCK + t * kTile;
     return __builtin_amdgcn_readfirstlane(static_cast<int>(tiles[t]) * kTile);
   };
   // Source offsets of tile t's copy; rows past L (tail tile only) repeat
@@ -839,11 +844,17 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int d0 = 32 * dt + 8 * rg + 4 * g;
-        u32x2 val = {pack_bf16x2(acc[dt][4 * rg] * inv, acc[dt][4 * rg + 1] * inv),
-                     pack_bf16x2(acc[dt][4 * rg + 2] * inv, acc[dt][4 * rg + 3] * inv)};
-        *reinterpret_cast<u32x2*>(orow + d0) = val;
+      for (int rp = 0; rp < 2; ++rp) {
+        // the lane's channels 16rp + 4g .. +3 and 16rp + 8 + 4g .. +3 of tile
+        // dt; exchanged with the lane of the other half, 8 in a row: half as
+        // many stores, 32 bytes a row each instead of 16
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          w[i] = pack_bf16x2(acc[dt][8 * rp + 2 * i] * inv, acc[dt][8 * rp + 2 * i + 1] * inv);
+        const auto e0 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+        const auto e1 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+        stg16(orow + 32 * dt + 16 * rp + 8 * g, u32x4{e0[0], e1[0], e0[1], e1[1]});
       }
     }
     if (lse != nullptr && g == 0)
