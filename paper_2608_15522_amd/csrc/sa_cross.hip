@@ -845,30 +845,108 @@ void launch_finalize(const float* colmass, float* sal_v_tok, float* sal_v_blk, i
 }
 
 // ---- fp32 path --------------------------------------------------------------
-// Both passes form 16 x 16 score tiles with v_mfma_f32_16x16x4_f32 (one
-// operand held in registers, the other streamed through each wave's own LDS
-// buffers, RowTile16) and take both directions in one launch (grid (a.n_wg + v.n_wg, P): the first a.n_wg
-// workgroups of a pair serve a->v, the rest v->a),
-// because either alone leaves most of the chip idle at the sizes fp32 is used
-// at.  At B1 H4 L_v4680 L_a512 d128 the two take 66 and 85 us (92 and 95 us
-// with the streamed operand loaded straight into registers); the
-// one-thread-per-row kernels before them took 39 ms.
+// Both passes form 16 x 16 score tiles with v_mfma_f32_16x16x4_f32, one
+// operand held in registers, the other streamed through LDS, and take both
+// directions in one launch (grid (a.n_wg + v.n_wg, P): the first a.n_wg
+// workgroups of a pair serve a->v, the rest v->a), because either alone leaves
+// most of the chip idle at the sizes fp32 is used at.
+// Log-sum-exps: 16 queries a workgroup, whose waves share out the key tiles,
+// each through LDS buffers of its own (RowTile16).  Column masses: 16 keys a
+// wave, four waves sharing the query tiles through one LDS ring (RowRing16);
+// launches of at most one workgroup a CU (SPLIT = 4) have 16 waves, four groups
+// that hold the same keys and share out the query tiles.  At B1 H4 L_v4680
+// L_a512 d128 the passes take 68 and 66 us; with rings private to a wave
+// the second took 85, a merge of the key chunks in a launch of its own 5 more.
 constexpr int kF32XWaves = 4;
-constexpr int kF32XKeys = 64;  // keys per column-mass workgroup, 16 per wave
+constexpr int kF32XRows = 16 * kF32XWaves;  // keys per column-mass workgroup
+constexpr int kF32XLse = 512;               // queries whose LSEs are in LDS at a time
+constexpr int kF32XMerge = 16;              // most LSE partials of a query
 
 // One direction's share of a launch.
 struct F32Dir {
   const float* q;   // [P][Lq][D]
   const float* k;   // [P][Lk][D]
-  float2* part;     // LSE pass: (max, sum) [P][nchunk][Lq], or NULL
-  float* lse2;      // [P][Lq] log2-sum-exp: written by the LSE pass when part
-                    // is NULL, read by the column-mass pass
+  float* lse2;      // log2-sum-exp over each key chunk [P][nlse][Lq]
   float* out;       // column mass [P][nchunk][Lk]
   int Lq, Lk;
-  int nt;           // 16-row query tiles (LSE) or 64-key tiles (column mass)
-  int nchunk;       // key chunks (LSE) or query chunks (column mass)
-  int chunk;        // keys or queries per chunk
-  int n_wg;         // nt * nchunk workgroups per pair
+  int nlse;         // key chunks of the LSE pass
+  int lse_chunk;    // keys per chunk, a multiple of 16
+  int nchunk;       // query chunks of the column-mass pass
+  int chunk;        // queries per chunk
+  int n_wg;         // workgroups per pair of the launch at hand
+};
+
+// LDS ring of 16-row tiles shared by a group of four waves: a tile's 1 KB spans are
+// copied by the waves in turn; slots are swizzled as in RowTile16.
+template <int D>
+struct RowRing16 {
+  static constexpr int kBytes = 16 * D * 4;
+  static constexpr int kCopies = kBytes / 1024 / kF32XWaves;  // per wave and tile
+  static constexpr int kStages = 3;
+  const char* lds;
+  uint32_t lds_addr;
+  int row[kCopies];
+  uint32_t col[kCopies];
+  int rd;
+
+  __device__ __forceinline__ void init(char* ring, int wave, int lane) {
+    lds = ring;
+    lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_void_t*)ring +
+                                              static_cast<uint32_t>(wave * kCopies * 1024));
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) {
+      const int chunk = 64 * (wave * kCopies + i) + lane;
+      row[i] = chunk / (D / 4);
+      col[i] = 16u * static_cast<uint32_t>((chunk % (D / 4)) ^ row[i]);
+    }
+    const int n = lane & 15, gk = lane >> 4;
+    rd = n * D * 4 + 16 * (gk ^ n);
+  }
+  // Rows [row0, row0 + 16) of the [L][D] matrix src (row0 < L) to stage st;
+  // rows past L repeat row L - 1.
+  __device__ __forceinline__ void copy(const float* src, int row0, int L, int st) const {
+    const char* base = reinterpret_cast<const char*>(src + static_cast<size_t>(row0) * D);
+    const int limit = L - 1 - row0;
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i)
+      lds_dma16(base, static_cast<uint32_t>(min(row[i], limit) * (D * 4)) + col[i],
+                __builtin_amdgcn_readfirstlane(lds_addr + st * kBytes + i * 1024));
+  }
+  // f(row, tile) for the tiles at rows r0, r0 + 16, ... < r1 <= L (none for r1
+  // <= r0), in T steps, the same for every group of the workgroup.  A barrier
+  // opens each tile; the copy of the second tile after it goes out right
+  // behind, into the stage that every wave has read before that barrier.
+  // Begins after a barrier of the caller's, where an earlier stream used the
+  // ring, and ends without copies in flight.
+  template <class F>
+  __device__ __forceinline__ void stream(const float* src, int r0, int r1, int L, int T,
+                                         F&& f) const {
+    const int own = r1 > r0 ? ceil_div(r1 - r0, 16) : 0;
+#pragma unroll
+    for (int t = 0; t < kStages - 1; ++t)
+      if (t < own) copy(src, r0 + 16 * t, L, t);
+    int st = 0;
+    for (int t = 0; t < T; ++t) {
+      // tile t has landed once at most the copies of t + 1 are out
+      if (t + 1 < own)
+        wait_vm<kCopies>();
+      else
+        wait_vm<0>();
+      __syncthreads();
+      f32x4 x[D / 16];
+      const char* tile = lds + st * kBytes;
+      if (t < own) {
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i)
+          x[i] = *reinterpret_cast<const f32x4*>(tile + (rd ^ (64 * i)));
+      }
+      const int free_st = st == 0 ? kStages - 1 : st - 1;
+      if (t + kStages - 1 < own) copy(src, r0 + 16 * (t + kStages - 1), L, free_st);
+      __builtin_amdgcn_sched_barrier(0);
+      if (t < own) f(r0 + 16 * t, x);
+      st = st + 1 == kStages ? 0 : st + 1;
+    }
+  }
 };
 
 template <int D>
@@ -912,11 +990,12 @@ row_lse2_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
   const bool second = static_cast<int>(blockIdx.x) >= a.n_wg;
   const F32Dir& p = second ? v : a;
   const int wg = static_cast<int>(blockIdx.x) - (second ? a.n_wg : 0);
-  const int qt = wg % p.nt, ch = wg / p.nt, pair = blockIdx.y;
+  const int nt = ceil_div(p.Lq, 16);
+  const int qt = wg % nt, ch = wg / nt, pair = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 15, gk = lane >> 4;
   const int Lq = p.Lq, Lk = p.Lk;
-  const int k0 = ch * p.chunk, k1 = min(k0 + p.chunk, Lk);
+  const int k0 = ch * p.lse_chunk, k1 = min(k0 + p.lse_chunk, Lk);
   f32x4 qf[D / 16];
   const float* kh = p.k + static_cast<size_t>(pair) * Lk * D;
   float m = -INFINITY, l = 0.f;
@@ -960,67 +1039,85 @@ row_lse2_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
     ml = red[0][threadIdx.x];
 #pragma unroll
     for (int w = 1; w < kF32XWaves; ++w) ml = merge_lse(ml, red[w][threadIdx.x]);
-    if (p.part != nullptr)
-      p.part[(static_cast<size_t>(pair) * p.nchunk + ch) * Lq + row] = ml;
-    else
-      p.lse2[static_cast<size_t>(pair) * Lq + row] = ml.x + log2f(ml.y);
+    p.lse2[(static_cast<size_t>(pair) * p.nlse + ch) * Lq + row] = ml.x + log2f(ml.y);
   }
 }
 
 // Column mass over a chunk of queries: out[pair][chunk][key] = sum over the
-// chunk's queries of 2^(c * q . k - lse2[q]).  A wave holds 16 keys (S^T =
-// K Q^T: a lane sums its keys 4gk .. 4gk+3 over the queries n, n+16, ...) and
-// streams the chunk's 16-query tiles; the 16 lanes of a key are added at the
-// end.
-template <int D>
-__global__ void __launch_bounds__(64 * kF32XWaves)
+// chunk's queries of 2^(c * q . k - lse2[q]).  A wave holds 16 keys (S = Q
+// K^T: a lane sums key n over the queries 4gk .. 4gk+3 of every tile) and
+// streams the chunk, kF32XLse queries at a time, whose LSEs are merged into
+// LDS first; the 4 lanes of a key are added at the end.
+template <int D, int SPLIT>
+__global__ void __launch_bounds__(64 * kF32XWaves * SPLIT) __attribute__((amdgpu_waves_per_eu(SPLIT > 1 ? 4 : 5)))
 colmass_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
-  __shared__ __attribute__((aligned(1024))) char ring[kF32XWaves * 2 * RowTile16<D>::kBytes];
+  constexpr int kRingBytes = RowRing16<D>::kStages * RowRing16<D>::kBytes;
+  __shared__ __attribute__((aligned(1024))) char ring_lds[SPLIT * kRingBytes];
+  __shared__ float red[SPLIT][kF32XRows];
+  __shared__ __attribute__((aligned(16))) float lse_s[kF32XLse];
   const bool second = static_cast<int>(blockIdx.x) >= a.n_wg;
   const F32Dir& p = second ? v : a;
   const int wg = static_cast<int>(blockIdx.x) - (second ? a.n_wg : 0);
-  const int kt = wg % p.nt, ch = wg / p.nt, pair = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = lane & 15, gk = lane >> 4;
   const int Lq = p.Lq, Lk = p.Lk;
-  const int key0 = kt * kF32XKeys + 16 * wave;
-  if (key0 >= Lk) return;
+  const int nt = ceil_div(Lk, kF32XRows);
+  const int kt = wg % nt, ch = wg / nt, pair = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % kF32XWaves;
+  const int part =
+      SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * kF32XWaves)) : 0;
+  const int n = lane & 15, gk = lane >> 4;
+  const int key = kt * kF32XRows + 16 * wave + n;
   const int q0 = ch * p.chunk, q1 = min(q0 + p.chunk, Lq);
   f32x4 kf[D / 16];
-  const float* qh = p.q + static_cast<size_t>(pair) * Lq * D;
-  const float* lh = p.lse2 + static_cast<size_t>(pair) * Lq;
-  float sum[4] = {0.f, 0.f, 0.f, 0.f};
-  auto load_lse = [&](int q) { return q + n < q1 ? lh[q + n] : INFINITY; };  // +inf: adds 0
-  RowTile16<D> tile;
-  tile.init(ring + wave * 2 * RowTile16<D>::kBytes, lane);
-  int buf = 0;
-  tile.copy(qh, q0, Lq, 0);
-  float ln = load_lse(q0);
-  load_row_f32<D>(p.k + static_cast<size_t>(pair) * Lk * D, key0 + n, Lk, gk, kf);
-  for (int q = q0; q < q1; q += 16) {
-    wait_dma();
-    __builtin_amdgcn_sched_barrier(0);
-    f32x4 qf[D / 16];
-    tile.read(buf, qf);
-    buf ^= 1;
-    const float lr = ln;
-    if (q + 16 < q1) {
-      tile.copy(qh, q + 16, Lq, buf);
-      ln = load_lse(q + 16);
+  load_row_f32<D>(p.k + static_cast<size_t>(pair) * Lk * D, key, Lk, gk, kf);
+  float sum = 0.f;
+  RowRing16<D> ring;
+  ring.init(ring_lds + part * kRingBytes, wave, lane);
+  for (int w0 = q0; w0 < q1; w0 += kF32XLse) {
+    const int w1 = min(w0 + kF32XLse, q1);
+    if (w0 > q0) __syncthreads();  // the previous window has been read
+    for (int i = threadIdx.x; i < kF32XLse; i += 64 * kF32XWaves * SPLIT) {
+      float x = INFINITY;  // past the chunk: adds 0
+      if (w0 + i < w1) {
+        const float* src = p.lse2 + static_cast<size_t>(pair) * p.nlse * Lq + w0 + i;
+        x = src[0];
+        if (p.nlse > 1) {
+          float y[kF32XMerge];
+#pragma unroll
+          for (int j = 0; j < kF32XMerge; ++j)
+            y[j] = j < p.nlse ? src[static_cast<size_t>(j) * Lq] : -INFINITY;
+#pragma unroll
+          for (int j = 1; j < kF32XMerge; ++j) x = fmaxf(x, y[j]);
+          float t = 0.f;
+#pragma unroll
+          for (int j = 0; j < kF32XMerge; ++j) t += exp2f(y[j] - x);
+          x = x == -INFINITY ? x : x + log2f(t);
+        }
+      }
+      lse_s[i] = x;
     }
-    __builtin_amdgcn_sched_barrier(0);
-    const f32x4 s = tile_f32<D>(kf, qf);
+    // the stream's first barrier makes them visible
+    const int T = ceil_div(ceil_div(w1 - w0, 16), SPLIT);
+    const int s0 = w0 + 16 * T * part;
+    ring.stream(p.q + static_cast<size_t>(pair) * Lq * D, s0, min(s0 + 16 * T, w1), Lq, T,
+                [&](int q, const f32x4 (&qf)[D / 16]) {
+      const f32x4 lr = *reinterpret_cast<const f32x4*>(&lse_s[q - w0 + 4 * gk]);
+      const f32x4 s = tile_f32<D>(qf, kf);
+      float t[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) sum[e] += fast_exp2(fmaf(s[e], c.hi, fmaf(s[e], c.lo, -lr)));
+      for (int e = 0; e < 4; ++e) t[e] = fast_exp2(fmaf(s[e], c.hi, fmaf(s[e], c.lo, -lr[e])));
+      sum += (t[0] + t[1]) + (t[2] + t[3]);
+    });
   }
+  sum += __shfl_xor(sum, 16, 64);
+  sum += __shfl_xor(sum, 32, 64);
+  if constexpr (SPLIT > 1) {
+    if (gk == 0) red[part][16 * wave + n] = sum;
+    __syncthreads();
+    if (part > 0) return;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) sum[e] += __shfl_xor(sum[e], o, 64);
-    const int key = key0 + 4 * gk + e;
-    if (n == 0 && key < Lk)
-      p.out[(static_cast<size_t>(pair) * p.nchunk + ch) * Lk + key] = sum[e];
+    for (int j = 1; j < SPLIT; ++j) sum += red[j][16 * wave + n];
   }
+  if (gk == 0 && key < Lk) p.out[(static_cast<size_t>(pair) * p.nchunk + ch) * Lk + key] = sum;
 }
 
 // Video keys per K1 or K2 workgroup: the multiple of 128 (whole blocks) up to
@@ -1132,41 +1229,50 @@ void cross_f32(const float* q_a, const float* k_v, const float* q_v,
                const float* k_a, int B, int H, int L_v, int L_a, float scale,
                int block, float* sal_v_tok, float* sal_v_blk, float* sal_a_tok,
                int accumulate, char* ws, hipStream_t s) {
-  const CrossWs lay = cross_ws_layout(B, H, L_v, L_a);
   const Log2Scale c = log2_scale(scale);
   const int P = B * H;
-  float2* lse_part = reinterpret_cast<float2*>(ws + lay.lse_part);
-  float* lse_a = reinterpret_cast<float*>(ws + lay.lse_a);
-  float* colmass = reinterpret_cast<float*>(ws + lay.colmass);
-  float* lse_v = reinterpret_cast<float*>(ws + lay.lse_v);
-  float* v2a_part = reinterpret_cast<float*>(ws + lay.v2a_part);
-  // Log2-sum-exps: a->v in chunks of 1024 video keys (merged below), v->a
-  // over all audio keys at once.
-  const int nchunk = ceil_div(L_v, kLseChunk);
-  auto dir = [&](const float* q, const float* k, float2* part, float* lse2, float* out, int Lq,
-                 int Lk, int nt, int nch, int chunk) {
-    return F32Dir{q, k, part, lse2, out, Lq, Lk, nt, nch, chunk, nt * nch};
+  const int nchunk3 = ceil_div(L_v, kV2aChunk);
+  const size_t n_v = static_cast<size_t>(P) * L_v, n_a = static_cast<size_t>(P) * L_a;
+  size_t off = 0;
+  auto take = [&](size_t n) {
+    float* p = reinterpret_cast<float*>(ws + off);
+    off += align_up(sizeof(float) * n);
+    return p;
   };
-  F32Dir a = dir(q_a, k_v, nchunk > 1 ? lse_part : nullptr, lse_a, nullptr, L_a, L_v,
-                 ceil_div(L_a, 16), nchunk, kLseChunk);
-  F32Dir v = dir(q_v, k_a, nullptr, lse_v, nullptr, L_v, L_a, ceil_div(L_v, 16), 1, L_a);
-  if (q_v == nullptr) v.n_wg = 0;
+  float* colmass = take(n_v);
+  float* lse_v = take(n_v);
+  float* v2a_part = take(n_a * nchunk3);
+  float* lse_a = take(0);
+  // Video keys per a->v log-sum-exp workgroup: 1024, or down to 256 while the
+  // launch has less than two workgroups a CU and the rest of the workspace holds
+  // the partials, which the column-mass workgroups merge where they read them
+  // (11.3 -> 5.5 us at B1 H2 L_v1024 L_a128 d64; at H8 L_v4680 L_a512 d128
+  // chunks of 400 keys were 10 us slower than 1024).
+  const bool rev = q_v != nullptr;
+  const long room = static_cast<long>((cross_ws_layout(B, H, L_v, L_a).total - off) / (sizeof(float) * n_a));
+  auto lse_wgs = [&](int chunk) {
+    return static_cast<long>(P) * (ceil_div(L_a, 16) * ceil_div(L_v, chunk) + (rev ? ceil_div(L_v, 16) : 0));
+  };
+  int lse_chunk = std::max(1024, ceil_div(ceil_div(L_v, kF32XMerge), 16) * 16);
+  while (lse_chunk > 256 && lse_wgs(lse_chunk) < 2 * kXcds * kCusPerXcd &&
+         ceil_div(L_v, lse_chunk / 2) <= std::min(room, static_cast<long>(kF32XMerge)))
+    lse_chunk /= 2;
+  const int nlse = ceil_div(L_v, lse_chunk);
+  F32Dir a{q_a, k_v, lse_a, colmass, L_a, L_v, nlse, lse_chunk, 1, L_a, 0};
+  F32Dir v{q_v, k_a, lse_v, v2a_part, L_v, L_a, 1, L_a, nchunk3, kV2aChunk, 0};
+  a.n_wg = ceil_div(L_a, 16) * nlse;
+  v.n_wg = rev ? ceil_div(L_v, 16) : 0;
   hipLaunchKernelGGL(row_lse2_f32_kernel<D>, dim3(a.n_wg + v.n_wg, P), dim3(64 * kF32XWaves), 0, s, a,
                      v, c);
-  if (nchunk > 1) {
-    const size_t nlse = static_cast<size_t>(P) * L_a;
-    hipLaunchKernelGGL(lse_combine_kernel, dim3((nlse + 15) / 16), dim3(256), 0, s, lse_part, lse_a,
-                       P, L_a, nchunk);
-  }
   // Column masses: a->v over all audio queries, v->a in chunks of 512 video
   // queries.
-  const int nchunk3 = ceil_div(L_v, kV2aChunk);
-  a = dir(q_a, k_v, nullptr, lse_a, colmass, L_a, L_v, ceil_div(L_v, kF32XKeys), 1, L_a);
-  v = dir(q_v, k_a, nullptr, lse_v, v2a_part, L_v, L_a, ceil_div(L_a, kF32XKeys), nchunk3,
-          kV2aChunk);
-  if (q_v == nullptr) v.n_wg = 0;
-  hipLaunchKernelGGL(colmass_f32_kernel<D>, dim3(a.n_wg + v.n_wg, P), dim3(64 * kF32XWaves), 0, s, a,
-                     v, c);
+  a.n_wg = ceil_div(L_v, kF32XRows);
+  v.n_wg = rev ? ceil_div(L_a, kF32XRows) * nchunk3 : 0;
+  const dim3 grid(a.n_wg + v.n_wg, P);
+  if (static_cast<long>(grid.x) * P <= kXcds * kCusPerXcd)
+    hipLaunchKernelGGL((colmass_f32_kernel<D, 4>), grid, dim3(4 * 64 * kF32XWaves), 0, s, a, v, c);
+  else
+    hipLaunchKernelGGL((colmass_f32_kernel<D, 1>), grid, dim3(64 * kF32XWaves), 0, s, a, v, c);
   launch_finalize(colmass, sal_v_tok, sal_v_blk, B, H, L_v, block, v2a_part,
                   q_v != nullptr ? sal_a_tok : nullptr, nchunk3, L_a, accumulate, s);
 }

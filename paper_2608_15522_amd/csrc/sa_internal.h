@@ -20,12 +20,13 @@ constexpr int kMaxPairs = 65535;  // largest B*H (a grid dimension indexes (b, h
 
 inline size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Workspace of sa_cross_scores (both dtypes are covered).
+// Workspace of sa_cross_scores.  The bf16 path's parts; the fp32 path lays its
+// own out within the same total.
 struct CrossWs {
   size_t lse_part;   // float2 [B,H,nchunk,L_a]  (m, l) partials, bf16 path
-  size_t lse_a;      // float  [B,H,L_a]         a->v log2-sum-exp, f32 path
+  size_t lse_a;      // float  [B,H,L_a]         (counted; not used by the bf16 path)
   size_t colmass;    // float  [B,H,L_v]         per-head a->v column mass
-  size_t lse_v;      // float  [B,H,L_v]         v->a log2-sum-exp, f32 path
+  size_t lse_v;      // float  [B,H,L_v]         (counted; not used by the bf16 path)
   size_t v2a_part;   // float  [B,H,nchunk3,L_a] v->a column-mass partials
   size_t v2a_head;   // float  [B,H,L_a]         a->v log2-sum-exp, bf16 path
   size_t total;

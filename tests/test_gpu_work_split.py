@@ -160,3 +160,26 @@ def test_sparse_attention_runs(H, n_b, tail, d, block, kind):
     o2, lse2 = torch.full_like(o, float("nan")), torch.full_like(lse, float("nan"))
     sa.sa_sparse_attention_noalloc(q, k, v, d**-0.5, block, idx, cnt, o2, lse2)
     assert torch.equal(o.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, lse2)
+
+
+# fp32 saliency: 16-wave and 4-wave column masses, key chunks of 256 to 1024
+# keys and of a sixteenth of the clip, two windows of audio queries, tails of
+# one row.  A term's error is that of its logit (2^-24 of |s| <= 8 or so, twice)
+# and of the sums' few roundings, relative to a positive sum: 1e-5 covers it.
+@pytest.mark.parametrize("H,L_v,L_a,d", [(2, 1024, 128, 64), (1, 300, 5, 128), (4, 4680, 513, 128),
+                                         (8, 2100, 40, 64), (1, 16500, 33, 64)])
+def test_saliency_f32_chunks(H, L_v, L_a, d):
+    print(f"case saliency f32 H={H} L_v={L_v} L_a={L_a} d={d}", flush=True)
+    scale = float(np.float32(d**-0.5))
+    q_a, k_a = (_randn(1, H, L_a, d, seed=i, dtype=torch.float32) for i in (1, 2))
+    q_v, k_v = (_randn(1, H, L_v, d, seed=i, dtype=torch.float32) for i in (3, 4))
+    ref_v = torch.zeros(L_v, dtype=torch.float64, device="cuda")
+    ref_a = torch.zeros(L_a, dtype=torch.float64, device="cuda")
+    for h in range(H):
+        ref_v += torch.softmax(scale * (q_a[0, h].double() @ k_v[0, h].double().T.contiguous()), 1).sum(0)
+        ref_a += torch.softmax(scale * (q_v[0, h].double() @ k_a[0, h].double().T.contiguous()), 1).sum(0)
+    v_tok, _, a_tok = sa.sa_cross_scores(q_a, k_v, q_v, k_a, scale, 64)
+    for x, ref in ((v_tok, ref_v / (H * L_a)), (a_tok, ref_a / (H * L_v))):
+        assert ((x[0].double() - ref).abs() <= 1e-5 * ref).all()
+    only_v = sa.sa_cross_scores(q_a, k_v, None, None, scale, 64)[0]  # one direction
+    assert ((only_v[0].double() - ref_v / (H * L_a)).abs() <= 1e-5 * ref_v / (H * L_a)).all()
