@@ -2,18 +2,18 @@
 // lagged saliency update (Eq. (4)).
 //
 // K8 saliency_ema: s_bar = alpha * s_bar + (1 - alpha) * s, elementwise fp32.
-// K9 select_tokens: per batch item one workgroup (one wave up to L = 2048,
+// K9 select_tokens: per batch item one workgroup (one wave up to L = 512,
 //    else 1024 threads) finds the k_tok-th smallest value key T (saliency
 //    descending) of the L tokens by a radix search: the bits that every key
-//    shares are decided by one AND/OR
-//    reduction, then each step decides two bits from the key counts of the
-//    prefix group per digit (DPP wave sums, one barrier with alternating LDS
-//    slots), until one key is left in the group.  Tokens tied at T are taken
-//    in index order.  Each wave owns a contiguous range of tokens (in
-//    registers up to L = 32768), read 64 consecutive tokens at a time,
-//    so ballot prefix counts and one scan of the per-wave totals write the
-//    kept tokens in ascending order.  Once the prefix group holds at most
-//    16384 keys they are copied to LDS and later steps scan only them.
+//    shares are decided by one AND/OR reduction, then each step decides eight
+//    bits from an LDS histogram of the prefix group's digits, until one key is
+//    left in the group.  Tokens tied at T are taken in index order.  Each wave
+//    owns a contiguous range of tokens (in registers up to L = 32768), read 64
+//    consecutive tokens at a time, so ballot prefix counts and one scan of the
+//    per-wave totals write the kept tokens in ascending order.
+//    Bound by latency: one workgroup, a chain of barriers.  Two bits a step
+//    (counts by wave sums, candidates copied to LDS) took 53 us at L =
+//    32760, 17 at 2049 and 10 at 512 against 26, 8 and 8.
 // The dense attention rows of the protected tokens are the gather variant of
 // the attention kernel (sa_attn.hip).
 #include "sa_device.h"
@@ -33,32 +33,7 @@ saliency_ema_kernel(float* __restrict__ s_bar, const float* __restrict__ s, size
 }
 
 // ---- K9 ---------------------------------------------------------------------
-constexpr int kTokCand = 16384;  // LDS candidates once the prefix group fits
-
-// Exclusive prefix of `v` over the workgroup (NW waves) in thread order, and
-// the total.  Ends with a barrier after the LDS slots are read.
-template <int NW>
-__device__ __forceinline__ int block_exclusive_scan(int v, int* wave_tot, int& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += u;
-  }
-  if (lane == 63) wave_tot[wave] = incl;
-  __syncthreads();
-  int base = 0;
-  total = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    const int t = wave_tot[w];
-    if (w < wave) base += t;
-    total += t;
-  }
-  __syncthreads();
-  return base + incl - v;
-}
+constexpr int kDigitBits = 8;  // bits decided per step
 
 // Exclusive prefix over the NW waves of a per-wave value (given by every
 // lane of the wave); ends with a barrier after the LDS slots are read.
@@ -83,15 +58,16 @@ __device__ __forceinline__ int wave_exclusive_base(int v, int* wave_tot) {
 // NT threads (NW = NT/64 waves); wave w owns the tokens [w*S, (w+1)*S),
 // S = ceil(L/NW); lane l holds tokens w*S + 64 j + l.  R > 0: the keys stay
 // in registers (64 R >= S); R == 0: they are read from global memory on
-// every pass.  Only the 1024-thread form copies candidates to LDS.
+// every pass.
 template <int R, int NT>
 __global__ void __launch_bounds__(NT)
 select_tokens_kernel(const float* __restrict__ sal, int L, int k_tok,
                      int32_t* __restrict__ tok_idx, uint8_t* __restrict__ tok_flag) {
   constexpr int NW = NT / 64;
-  constexpr bool kCompact = NW > 1;
-  __shared__ uint32_t cand[kCompact ? kTokCand : 1];
-  __shared__ uint32_t cnt_sh[2][NW][4];
+  constexpr int kDigits = 1 << kDigitBits;
+  static_assert(kDigits == 4 * 64, "a lane of wave 0 scans four digits");
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kDigits];
+  __shared__ int sel_sh[3];
   __shared__ uint32_t red_sh[NW][2];
   __shared__ int wave_tot[NW];
   const int b = blockIdx.x;
@@ -122,11 +98,16 @@ select_tokens_kernel(const float* __restrict__ sal, int L, int k_tok,
         f(vk[j], i, i < w1);
       }
     } else {
-      for (int j = 0; j < J; ++j) {
-        const int i = w0 + 64 * j + lane;
-        const bool ok = i < w1;
-        const float x = s[min(i, L - 1)];
-        f(ok ? ~float_order_key(x) : 0u, i, ok);
+      for (int j0 = 0; j0 < J; j0 += 8) {  // eight loads in flight
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = s[min(w0 + 64 * (j0 + u) + lane, L - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int i = w0 + 64 * (j0 + u) + lane;
+          const bool ok = i < w1;
+          f(ok ? ~float_order_key(x[u]) : 0u, i, ok);
+        }
       }
     }
   };
@@ -163,80 +144,44 @@ select_tokens_kernel(const float* __restrict__ sal, int L, int k_tok,
     int hb = diff != 0u ? 31 - __clz(diff) : -1;  // highest undecided bit
     fixed = hb >= 0 ? ~static_cast<uint32_t>((2ull << hb) - 1ull) : 0xffffffffu;
     prefix = a & fixed;
-    bool in_lds = false;
-    int n_cand = 0;
-    // two bits per step: count the keys of the prefix group by digit
-    for (int step = 0; hb >= 0 && size > 1; ++step) {
-      if (kCompact && !in_lds && size <= kTokCand) {
-        // the group's keys go to LDS and later steps scan only them
-        int mine_c = 0;
-        for_keys([&](uint32_t key) { mine_c += (key & fixed) == prefix; });
-        int tot = 0;
-        int at = block_exclusive_scan<NW>(mine_c, wave_tot, tot);
-        for_keys([&](uint32_t key) {
-          if ((key & fixed) == prefix) cand[at++] = key;
-        });
-        __syncthreads();
-        in_lds = true;
-        n_cand = size;
-      }
-      const int lo = hb > 0 ? hb - 1 : 0;
-      uint32_t c0 = 0u, c1 = 0u, c2 = 0u;
-      auto count = [&](uint32_t key) {
-        const bool in = (key & fixed) == prefix;
-        const uint32_t dg = (key >> lo) & 3u;
-        c0 += in && dg == 0u;
-        c1 += in && dg == 1u;
-        c2 += in && dg == 2u;
-      };
-      if (in_lds) {
-        // all slots of this thread at once; reads stay inside `cand`
-        constexpr int U = kCompact ? kTokCand / NT : 1;
+    while (hb >= 0 && size > 1) {
+      const int lo = max(hb - (kDigitBits - 1), 0);
+      const uint32_t digit_mask = (2u << (hb - lo)) - 1u;
+      for (int i = tid; i < kDigits; i += NT) hist[i] = 0u;
+      __syncthreads();
+      for_keys([&](uint32_t key) {
+        if ((key & fixed) == prefix) atomicAdd(&hist[(key >> lo) & digit_mask], 1u);
+      });
+      __syncthreads();
+      if (wave == 0) {
+        // the digit that holds the k_tok-th key, in the lane of its four
+        const u32x4 h = *reinterpret_cast<const u32x4*>(&hist[4 * lane]);
+        int incl = static_cast<int>(h[0] + h[1] + h[2] + h[3]);
+        int at = below - incl;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int i = tid + u * NT;
-          const uint32_t key = cand[min(i, kTokCand - 1)];
-          if (i < n_cand) count(key);
+        for (int o = 1; o < 64; o <<= 1) {
+          const int u = __shfl_up(incl, o, 64);
+          if (lane >= o) incl += u;
         }
-      } else {
-        for_keys(count);
-      }
-      c0 = __reduce_add_sync(~0ull, c0);
-      c1 = __reduce_add_sync(~0ull, c1);
-      c2 = __reduce_add_sync(~0ull, c2);
-      if (lane == 0) {
-        cnt_sh[step & 1][wave][0] = c0;
-        cnt_sh[step & 1][wave][1] = c1;
-        cnt_sh[step & 1][wave][2] = c2;
+        at += incl;  // keys below the lane's digits
+        if (at < k_tok && below + incl >= k_tok) {
+          int j = 0;
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (j == e && at + static_cast<int>(h[e]) < k_tok) {
+              at += static_cast<int>(h[e]);
+              j = e + 1;
+            }
+          sel_sh[0] = 4 * lane + j;
+          sel_sh[1] = at;
+          sel_sh[2] = static_cast<int>(j == 0 ? h[0] : j == 1 ? h[1] : j == 2 ? h[2] : h[3]);
+        }
       }
       __syncthreads();
-      int n0 = 0, n1 = 0, n2 = 0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        n0 += static_cast<int>(cnt_sh[step & 1][w][0]);
-        n1 += static_cast<int>(cnt_sh[step & 1][w][1]);
-        n2 += static_cast<int>(cnt_sh[step & 1][w][2]);
-      }
-      uint32_t dsel;
-      if (below + n0 >= k_tok) {
-        dsel = 0u;
-        size = n0;
-      } else if (below + n0 + n1 >= k_tok) {
-        dsel = 1u;
-        below += n0;
-        size = n1;
-      } else if (below + n0 + n1 + n2 >= k_tok) {
-        dsel = 2u;
-        below += n0 + n1;
-        size = n2;
-      } else {
-        dsel = 3u;
-        size -= n0 + n1 + n2;
-        below += n0 + n1 + n2;
-      }
-      const uint32_t width = hb > 0 ? 3u : 1u;
-      fixed |= width << lo;
-      prefix |= dsel << lo;
+      prefix |= static_cast<uint32_t>(sel_sh[0]) << lo;
+      fixed |= digit_mask << lo;
+      below = sel_sh[1];
+      size = sel_sh[2];
       hb = lo - 1;
     }
   }
@@ -299,11 +244,11 @@ void launch_select_protected_tokens(const float* sal_tok, int B, int L, int k_to
 #define SA_SELECT(R, NT)                                                                 \
   hipLaunchKernelGGL((select_tokens_kernel<R, NT>), grid, dim3(NT), 0, st, sal_tok, L, k_tok, \
                      tok_idx, tok_flag)
-  if (L <= 512) {  // one wave: tokens per lane ceil(L/64)
+  // One wave up to 512 tokens (no barrier costs anything there); from there on
+  // 16 waves (8 us at 2049 tokens, one wave with 32 tokens a lane 15 at 2048).
+  if (L <= 512) {
     SA_SELECT(8, 64);
-  } else if (L <= 2048) {
-    SA_SELECT(32, 64);
-  } else {  // 16 waves: tokens per lane ceil(ceil(L/16)/64)
+  } else {  // tokens per lane ceil(ceil(L/16)/64)
     const int J = ceil_div(ceil_div(L, 16), 64);
     if (J <= 4)
       SA_SELECT(4, 1024);

@@ -183,3 +183,25 @@ def test_saliency_f32_chunks(H, L_v, L_a, d):
         assert ((x[0].double() - ref).abs() <= 1e-5 * ref).all()
     only_v = sa.sa_cross_scores(q_a, k_v, None, None, scale, 64)[0]  # one direction
     assert ((only_v[0].double() - ref_v / (H * L_a)).abs() <= 1e-5 * ref_v / (H * L_a)).all()
+
+
+# token selection by digits of eight bits: both sides of every register form,
+# keys that differ in the last bits only, in the sign, in few values, in none
+@pytest.mark.parametrize("L", [1, 65, 512, 513, 4096, 4097, 16385, 32768, 32769, 70001])
+@pytest.mark.parametrize("kind", ["map", "adjacent", "signs", "few", "equal"])
+def test_token_selection_digits(L, kind):
+    rng = np.random.default_rng(L)
+    s = {"map": np.exp(rng.standard_normal((2, L))),
+         "adjacent": (np.float32(1.0).view(np.int32) + rng.integers(0, 300, (2, L))).astype(np.int32)
+         .view(np.float32),
+         "signs": rng.standard_normal((2, L)) * 10.0 ** rng.integers(-30, 30, (2, L)),
+         "few": rng.integers(-2, 3, (2, L)) * 0.25, "equal": np.full((2, L), 0.5)}[kind]
+    s = s.astype(np.float32)
+    for k in sorted({1, max(1, L // 20), max(1, L - 1)}):
+        idx, flag = sa.sa_select_protected_tokens(torch.from_numpy(s).cuda(), k)
+        for b in range(2):
+            want = np.sort(np.argsort(-s[b], kind="stable")[:k])
+            assert np.array_equal(idx[b].cpu().numpy(), want), (L, kind, k)
+            ref = np.zeros(L, np.uint8)
+            ref[want] = 1
+            assert np.array_equal(flag[b].cpu().numpy(), ref)
