@@ -283,7 +283,8 @@ int sa_build_block_mask_pooled(const double* qbar, const double* kbar, int B,
  *              logits of each row, nullable
  *   kv_idx     [B,H,n_b,n_b] i32; entries outside [0,n_b) are ignored
  *   kv_cnt     [B,H,n_b] i32, clamped to [0,n_b]; a row with no valid entry
- *              outputs zeros and lse = -inf
+ *              outputs zeros and lse = -inf (a key whose logit is -inf weighs
+ *              0; a row of such keys only is a row without a key)
  *   ws         workspace of sa_workspace_size(SA_CALL_SPARSE_ATTENTION) bytes.
  *              bf16 calls of few rows (n_b >= 64, at most four rows per
  *              workgroup slot of the chip) may cut the lists of their rows

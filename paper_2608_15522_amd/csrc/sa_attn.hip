@@ -34,6 +34,8 @@
 //
 // f32 path: fp32 matrix products (v_mfma_f32_16x16x4_f32) from operands held
 // in registers, the keys of a 16-row block split over the workgroup's waves.
+#include <float.h>
+
 #include <algorithm>
 
 #include "sa_device.h"
@@ -518,7 +520,11 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
   f32x16 acc[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) acc[dt] = zero16();
-  float m = -INFINITY;
+  // The running reference starts at the lowest finite value: against it a logit
+  // of -inf weighs 0 from the first tile on, while -inf - -inf is a NaN that no
+  // later tile repairs.  A list may begin with keys of -inf logits, and so may
+  // any run or key split of a list that does not.
+  float m = -FLT_MAX;
   float lsum = 0.f;
   typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
   const bf16x2_t ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};

@@ -1,0 +1,98 @@
+"""Keys whose logits are -inf (a bias channel of -inf, as padding masks make
+them) weigh 0 wherever they lie: at the start of a list, over whole key blocks,
+at the start of a run, key split or chunk.  Against fp64 torch."""
+import math
+
+import pytest
+import torch
+
+import paper_2608_15522_amd as sa
+
+pytestmark = pytest.mark.gpu
+
+# key ranges of -inf logits, of L = 8200 keys: one key first, several tiles
+# first, across and inside the blocks that runs, splits and chunks begin at
+L = 8200
+SEGMENTS = {"first1": (0, 1), "first200": (0, 200), "mid": (512, 600), "blocks": (1024, 1664),
+            "half": (4100, 8200), "single": (2733, 2734)}
+
+
+def _randn(*shape, seed, dtype):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randn(*shape, generator=g, device="cuda").to(dtype)
+
+
+def _masked_inputs(H, Lq, d, seg, dtype):
+    """q [1,H,Lq,d] with a bias channel of ones, k, v [1,H,L,d] with -inf there
+    on the keys of `seg`, and the fp64 probabilities and row LSEs."""
+    q = _randn(1, H, Lq, d, seed=1, dtype=dtype)
+    k, v = (_randn(1, H, L, d, seed=i, dtype=dtype) for i in (2, 3))
+    q[..., 0] = 1
+    k[:, :, slice(*SEGMENTS[seg]), 0] = -math.inf
+    s = d**-0.5 * (q[0].double() @ k[0].double().transpose(1, 2).contiguous())
+    return q, k, v, torch.softmax(s, 2), torch.logsumexp(s, 2)
+
+
+def _rows_close(o, ref, rel):
+    """2-norm over a row's channels, relative to the row."""
+    assert torch.isfinite(o).all()
+    assert ((o.double() - ref).norm(dim=-1) <= rel * ref.norm(dim=-1)).all()
+
+
+# bf16: P and O are rounded to 2^-9 each, independently from key to key: 2.3e-3
+# of a row's norm, taken four times
+REL_O = {torch.bfloat16: 1e-2}
+TOL_LSE = {torch.bfloat16: 2.5e-3}
+
+
+@pytest.mark.parametrize("seg", SEGMENTS)
+@pytest.mark.parametrize("d,block,dtype", [(128, 128, torch.bfloat16), (64, 64, torch.bfloat16),
+                                           (128, 64, torch.bfloat16), (64, 128, torch.bfloat16)])
+def test_attention(seg, d, block, dtype):
+    H = 2
+    print(f"case -inf attention {seg} d={d} block={block} {dtype}", flush=True)
+    q, k, v, p, lse_ref = _masked_inputs(H, L, d, seg, dtype)
+    ref = p @ v[0].double()
+    del p
+    n_b = -(-L // block)
+    idx = torch.arange(n_b, dtype=torch.int32, device="cuda").expand(1, H, n_b, n_b).contiguous()
+    cnt = torch.full((1, H, n_b), n_b, dtype=torch.int32, device="cuda")
+    # lists in one piece, and with room to cut them into runs
+    least = 2 * -(-4 * H * n_b // 256) * 256 + 2048
+    full = sa.sa_workspace_size(sa.SA_CALL_SPARSE_ATTENTION, 1, H, L, 1, d, block)
+    for n in (least, full):
+        ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
+        o, lse = sa.sa_sparse_attention(q, k, v, d**-0.5, block, idx, cnt, want_lse=True, ws=ws)
+        _rows_close(o[0], ref, REL_O[dtype])
+        assert (lse[0].double() - lse_ref).abs().max() <= TOL_LSE[dtype]
+    # dense rows of chosen tokens (key splits)
+    tok = torch.arange(0, L, 7, dtype=torch.int32, device="cuda")[None].contiguous()
+    o, lse = torch.zeros_like(q), torch.zeros(1, H, L, device="cuda")
+    sa.sa_protected_token_attention(q, k, v, d**-0.5, tok, o, lse)
+    at = tok[0].long()
+    _rows_close(o[0][:, at], ref[:, at], REL_O[dtype])
+    assert (lse[0][:, at].double() - lse_ref[:, at]).abs().max() <= TOL_LSE[dtype]
+
+
+@pytest.mark.parametrize("seg", SEGMENTS)
+@pytest.mark.parametrize("d", [64, 128])
+def test_cross_attention(seg, d):
+    print(f"case -inf cross attention {seg} d={d}", flush=True)
+    q, k, v, p, lse_ref = _masked_inputs(2, 300, d, seg, torch.bfloat16)
+    o, lse = sa.sa_cross_attention(q, k, v, d**-0.5, want_lse=True)
+    _rows_close(o[0], p @ v[0].double(), REL_O[torch.bfloat16])
+    assert (lse[0].double() - lse_ref).abs().max() <= TOL_LSE[torch.bfloat16]
+
+
+def test_rows_of_infinite_logits_only():
+    """A list whose keys all carry -inf logits has no key that weighs: zeros
+    and lse = -inf, as for a list without a valid entry."""
+    H, n_b, d, block = 1, 70, 64, 64
+    n = n_b * block
+    q, k, v = (_randn(1, H, n, d, seed=i, dtype=torch.bfloat16) for i in (1, 2, 3))
+    q[..., 0] = 1
+    k[:, :, :2 * block, 0] = -math.inf
+    idx = torch.arange(n_b, dtype=torch.int32, device="cuda").expand(1, H, n_b, n_b).contiguous()
+    cnt = torch.full((1, H, n_b), 2, dtype=torch.int32, device="cuda")
+    o, lse = sa.sa_sparse_attention(q, k, v, d**-0.5, block, idx, cnt, want_lse=True)
+    assert (o == 0).all() and torch.isneginf(lse).all()
