@@ -1148,7 +1148,7 @@ sparse_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
     float p[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      p[e] = fast_exp2(fmaf(s[e], c.hi, fmaf(s[e], c.lo, -mref)));
+      p[e] = fast_exp2(log2_score(s[e], c, mref));
     if (x.key0 + kF32Keys > L) {  // rows past L weigh nothing, whatever row L-1 holds
 #pragma unroll
       for (int e = 0; e < 4; ++e)

@@ -1023,7 +1023,7 @@ row_lse2_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
     const float mref = m == -INFINITY ? 0.f : m;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float x = fast_exp2(fmaf(s[e], c.hi, fmaf(s[e], c.lo, -mref)));
+      const float x = fast_exp2(log2_score(s[e], c, mref));
       l += key + 4 * gk + e < k1 ? x : 0.f;
     }
   }
@@ -1104,7 +1104,7 @@ colmass_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
       const f32x4 s = tile_f32<D>(qf, kf);
       float t[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) t[e] = fast_exp2(fmaf(s[e], c.hi, fmaf(s[e], c.lo, -lr[e])));
+      for (int e = 0; e < 4; ++e) t[e] = fast_exp2(log2_score(s[e], c, lr[e]));
       sum += (t[0] + t[1]) + (t[2] + t[3]);
     });
   }

@@ -50,11 +50,18 @@ __device__ __forceinline__ f32x4 ldg_f32x4(const float* p) {
   return *reinterpret_cast<const f32x4*>(p);
 }
 
-// scale * log2(e) as an fp32 pair: s * hi + s * lo carries the product to
-// about 2^-48, so a score's error is that of its dot product.
+// scale * log2(e) as an fp32 pair: the product's own rounding (2^-24 of it with
+// one fp32 factor) drops out of a score.
 struct Log2Scale {
   float hi, lo;
 };
+// c * s - ref in two FMAs, good to an ulp of the larger of ref and the result.
+// s = -inf takes no low part: lo is negative for some scales (d = 128), and
+// -inf * lo + -inf * hi would be a NaN where the weight is 0.
+__device__ __forceinline__ float log2_score(float s, Log2Scale c, float ref) {
+  const float t = s == -INFINITY ? 0.f : s;
+  return fmaf(s, c.hi, fmaf(t, c.lo, -ref));
+}
 inline Log2Scale log2_scale(float scale) {
   const double c = static_cast<double>(scale) * 1.4426950408889634;
   const float hi = static_cast<float>(c);

@@ -40,14 +40,16 @@ def _rows_close(o, ref, rel):
 
 
 # bf16: P and O are rounded to 2^-9 each, independently from key to key: 2.3e-3
-# of a row's norm, taken four times
-REL_O = {torch.bfloat16: 1e-2}
-TOL_LSE = {torch.bfloat16: 2.5e-3}
+# of a row's norm, taken four times; fp32: the bound of the other parity tests
+# (1e-5 on values near 1) on rows of norm sqrt(d / keys) or so
+REL_O = {torch.bfloat16: 1e-2, torch.float32: 1e-5}
+TOL_LSE = {torch.bfloat16: 2.5e-3, torch.float32: 1e-5}
 
 
 @pytest.mark.parametrize("seg", SEGMENTS)
 @pytest.mark.parametrize("d,block,dtype", [(128, 128, torch.bfloat16), (64, 64, torch.bfloat16),
-                                           (128, 64, torch.bfloat16), (64, 128, torch.bfloat16)])
+                                           (128, 64, torch.bfloat16), (64, 128, torch.bfloat16),
+                                           (64, 64, torch.float32), (128, 128, torch.float32)])
 def test_attention(seg, d, block, dtype):
     H = 2
     print(f"case -inf attention {seg} d={d} block={block} {dtype}", flush=True)
@@ -82,6 +84,23 @@ def test_cross_attention(seg, d):
     o, lse = sa.sa_cross_attention(q, k, v, d**-0.5, want_lse=True)
     _rows_close(o[0], p @ v[0].double(), REL_O[torch.bfloat16])
     assert (lse[0].double() - lse_ref).abs().max() <= TOL_LSE[torch.bfloat16]
+
+
+def _check_saliency(L_a, d, seg, dtype, rel):
+    H = 2
+    q, k, _, p, _ = _masked_inputs(H, L_a, d, seg, dtype)
+    ref = p.sum((0, 1)) / (H * L_a)
+    got = sa.sa_cross_scores(q, k, None, None, d**-0.5, 64)[0][0].double()
+    assert torch.isfinite(got).all()
+    assert ((got - ref).abs() <= rel * ref).all()  # masked keys: exactly 0
+
+
+# whole and ragged 16-query tiles; the bound of the other fp32 saliency tests
+@pytest.mark.parametrize("seg", SEGMENTS)
+@pytest.mark.parametrize("L_a,d", [(512, 128), (37, 128), (512, 64), (37, 64)])
+def test_saliency_f32(seg, L_a, d):
+    print(f"case -inf saliency f32 {seg} L_a={L_a} d={d}", flush=True)
+    _check_saliency(L_a, d, seg, torch.float32, 1e-5)
 
 
 def test_rows_of_infinite_logits_only():
