@@ -28,6 +28,8 @@
 // All bf16 kernels share one key-stream engine (below).  No atomics: every
 // output element has one writer, so results are reproducible.
 // fp32 inputs run the same two passes on fp32 matrix products (fp32 path below).
+#include <float.h>
+
 #include <algorithm>
 
 #include "sa_device.h"
@@ -216,7 +218,8 @@ __device__ __forceinline__ void stream_keys(const KeyRing<D>& ring, const char* 
 
 // Lane-local online log2-sum-exp over the keys of KEYS_A units, for the two
 // query columns of the lane.  The running max m starts at the max of unit 0
-// and is raised only when a unit's sum against it reaches kSumGuard, so the
+// (the lowest finite value at least: against it units whose scores are all
+// -inf, wherever a chunk begins, weigh 0 instead of -inf - -inf) and is raised only when a unit's sum against it reaches kSumGuard, so the
 // per-score work is one FMA, one exp2 and one add.  Keys >= key_end (tail of
 // the last tile) are masked to -inf.
 template <int D>
@@ -237,7 +240,7 @@ struct LseAcc {
       float mx = x[h][0];
 #pragma unroll
       for (int i = 1; i < 16; ++i) mx = fmaxf(mx, x[h][i]);
-      m[h] = mx * c;
+      m[h] = fmaxf(mx * c, -FLT_MAX);
       l[h] = 0.f;
     }
   }

@@ -103,6 +103,16 @@ def test_saliency_f32(seg, L_a, d):
     _check_saliency(L_a, d, seg, torch.float32, 1e-5)
 
 
+# L_a = 512: whole query slabs, as rows past L_a hold zeros (0 * -inf); chunks of
+# 128 to 1024 video keys by the number of heads.  The bound of the other bf16
+# saliency tests.
+@pytest.mark.parametrize("seg", SEGMENTS)
+@pytest.mark.parametrize("d", [64, 128])
+def test_saliency_bf16(seg, d):
+    print(f"case -inf saliency bf16 {seg} d={d}", flush=True)
+    _check_saliency(512, d, seg, torch.bfloat16, 1e-4)
+
+
 def test_rows_of_infinite_logits_only():
     """A list whose keys all carry -inf logits has no key that weighs: zeros
     and lse = -inf, as for a list without a valid entry."""
