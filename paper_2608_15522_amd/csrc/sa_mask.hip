@@ -24,9 +24,10 @@ namespace sa {
 namespace {
 
 // ---- K4 ---------------------------------------------------------------------
-// Grid (ceil(n_b / kSelBlocks), B), 256 threads.  Every workgroup holds the
+// Grid (B, ceil(n_b / kSelBlocks)), 256 threads: B is bounded by nothing else, and
+// only the first grid dimension goes beyond 65535.  Every workgroup holds the
 // batch item's keys in LDS and ranks kSelBlocks of its blocks: kSelParts
-// threads per block each count the smaller keys in a quarter of the list, and
+// threads per block each count the smaller keys in an eighth of the list, and
 // the rank (keys are distinct) places the block.  No barrier chain: 36 bitonic
 // steps of one 1024-thread workgroup took 7.4 us at n_b = 256, two batch
 // items of n_b = 141 took 14.
@@ -37,13 +38,13 @@ select_protected_kernel(const float* __restrict__ sal_blk, int n_b, int k_prot,
                         int32_t* __restrict__ prot_idx, uint8_t* __restrict__ prot_flag) {
   __shared__ uint64_t keys[kMaxBlocks];
   __shared__ int cnt[kSelParts][kSelBlocks];
-  const int b = blockIdx.y, tid = threadIdx.x;
+  const int b = blockIdx.x, tid = threadIdx.x;
   const float* s = sal_blk + static_cast<size_t>(b) * n_b;
   for (int i = tid; i < n_b; i += 256)
     keys[i] = desc_value_asc_index_key(s[i], static_cast<uint32_t>(i));
   __syncthreads();
   const int t = tid % kSelBlocks, part = tid / kSelBlocks;
-  const int c = blockIdx.x * kSelBlocks + t;
+  const int c = blockIdx.y * kSelBlocks + t;
   const uint64_t mine = keys[min(c, n_b - 1)];
   const int j0 = n_b * part / kSelParts, j1 = n_b * (part + 1) / kSelParts;
   int below = 0;
@@ -437,7 +438,7 @@ void launch_mask_build(int E, dim3 grid, hipStream_t s, const double* qbar,
 void launch_select_protected(const float* sal_blk, int B, int n_b, int k_prot,
                              int32_t* prot_idx, uint8_t* prot_flag,
                              hipStream_t s) {
-  hipLaunchKernelGGL(select_protected_kernel, dim3(ceil_div(n_b, kSelBlocks), B), dim3(256), 0, s,
+  hipLaunchKernelGGL(select_protected_kernel, dim3(B, ceil_div(n_b, kSelBlocks)), dim3(256), 0, s,
                      sal_blk, n_b, k_prot, prot_idx, prot_flag);
 }
 

@@ -31,6 +31,20 @@ def test_block_ranking(n_b):
             assert np.array_equal(flag[b].cpu().numpy(), ref)
 
 
+# more batch items than the second and third grid dimensions hold
+@pytest.mark.parametrize("n_b", [1, 40])
+def test_block_ranking_of_many_items(n_b):
+    B = 65536 + 7
+    print(f"case ranking B={B} n_b={n_b}", flush=True)
+    s = _randn(B, n_b, seed=n_b, dtype=torch.float32).round_(decimals=1)  # ties
+    k = (n_b + 2) // 3
+    idx, flag = sa.sa_select_protected(s, k)
+    want = torch.sort(s, dim=1, descending=True, stable=True)[1][:, :k]
+    assert torch.equal(idx.long(), want)
+    ref = torch.zeros_like(flag).scatter_(1, want, 1)
+    assert torch.equal(flag, ref)
+
+
 # 1, 2, 4 and 8 blocks per pooling workgroup (768 workgroups are wanted)
 @pytest.mark.parametrize("H,n_b,tail,dtype", [(24, 7, 5, torch.bfloat16), (64, 24, 64, torch.bfloat16),
                                               (64, 47, 1, torch.float32), (64, 97, 33, torch.bfloat16)])
