@@ -565,7 +565,9 @@ lse_combine_kernel(const float2* __restrict__ part, float* __restrict__ lse2, in
   const int ph = threadIdx.x >> 4, jj = threadIdx.x & 15;
   const size_t n = static_cast<size_t>(P) * L_a;
   const size_t t = static_cast<size_t>(blockIdx.x) * 16 + jj;
-  float M = -INFINITY, S = 0.f;
+  // Every chunk counts, by its finite maximum (ph without a chunk: the lowest, and
+  // a sum of 0): one whose sum is a NaN makes the value a NaN.
+  float M = -FLT_MAX, S = 0.f;
   if (t < n) {
     const float2* p = part + t / L_a * nchunk * L_a + t % L_a;
     for (int c0 = ph; c0 < nchunk; c0 += 4 * kCombPhases) {
@@ -573,15 +575,14 @@ lse_combine_kernel(const float2* __restrict__ part, float* __restrict__ lse2, in
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int c = c0 + k * kCombPhases;
-        v[k] = c < nchunk ? p[static_cast<size_t>(c) * L_a] : make_float2(-INFINITY, 0.f);
+        v[k] = c < nchunk ? p[static_cast<size_t>(c) * L_a] : make_float2(-FLT_MAX, 0.f);
       }
       float m = M;
 #pragma unroll
       for (int k = 0; k < 4; ++k) m = fmaxf(m, v[k].x);
-      float s = S > 0.f ? S * fast_exp2(M - m) : 0.f;
+      float s = S * fast_exp2(M - m);
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (v[k].y > 0.f) s += v[k].y * fast_exp2(v[k].x - m);
+      for (int k = 0; k < 4; ++k) s += v[k].y * fast_exp2(v[k].x - m);
       M = m;
       S = s;
     }
@@ -595,7 +596,7 @@ lse_combine_kernel(const float2* __restrict__ part, float* __restrict__ lse2, in
 #pragma unroll
   for (int k = 0; k < kCombPhases; ++k) {
     const float2 v = red[k][jj];
-    if (v.y > 0.f) S += v.y * fast_exp2(v.x - M);
+    S += v.y * fast_exp2(v.x - M);
   }
   lse2[t] = M + __log2f(S);
 }

@@ -1,6 +1,7 @@
 """Keys whose logits are -inf (a bias channel of -inf, as padding masks make
 them) weigh 0 wherever they lie: at the start of a list, over whole key blocks,
-at the start of a run, key split or chunk.  Against fp64 torch."""
+at the start of a run, key split or chunk.  Against fp64 torch.  And a logit that is a
+NaN leaves no finite saliency."""
 import math
 
 import pytest
@@ -125,3 +126,14 @@ def test_rows_of_infinite_logits_only():
     cnt = torch.full((1, H, n_b), 2, dtype=torch.int32, device="cuda")
     o, lse = sa.sa_sparse_attention(q, k, v, d**-0.5, block, idx, cnt, want_lse=True)
     assert (o == 0).all() and torch.isneginf(lse).all()
+
+
+@pytest.mark.parametrize("L_v", [700, 8200])  # chunks of 128 and more keys
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_saliency_with_a_nan_key(L_v, dtype):
+    """The normaliser of every query is a NaN, and so is all it divides."""
+    print(f"case NaN saliency L_v={L_v} {dtype}", flush=True)
+    q, k = (_randn(1, 2, n, 64, seed=i, dtype=dtype) for i, n in ((1, 512), (2, L_v)))
+    k[0, 0, L_v // 2, 5] = math.nan
+    v_tok, v_blk, _ = sa.sa_cross_scores(q, k, None, None, 0.125, 64)
+    assert torch.isnan(v_tok).all() and torch.isnan(v_blk).all()
