@@ -1144,7 +1144,9 @@ sparse_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[dq][e] *= alpha;
     }
-    const float mref = m == -INFINITY ? 0.f : m;  // only -inf scores so far: they weigh 0
+    // only -inf scores so far: they weigh 0.  The slack is taken off the weights,
+    // which so stay at most 1 and keep P V within the range of V.
+    const float mref = m == -INFINITY ? 0.f : m + kRescaleSlack;
     float p[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e)
@@ -1224,7 +1226,8 @@ sparse_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
     *reinterpret_cast<f32x4*>(o + (static_cast<size_t>(pair) * L + orow) * D + d4) = val;
     if (lse != nullptr && d4 == 0)
       lse[static_cast<size_t>(pair) * L + orow] =
-          den > 0.f ? static_cast<float>(static_cast<double>(M) * 0.6931471805599453 +
+          den > 0.f ? static_cast<float>((static_cast<double>(M) + kRescaleSlack) *
+                                             0.6931471805599453 +
                                          static_cast<double>(logf(den)))
                 : -INFINITY;
   }

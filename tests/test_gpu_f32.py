@@ -55,3 +55,26 @@ def test_f32_token_rows_at_tile_edges(L, k_tok, d):
             ref = np.exp(s - ref_lse[:, None]) @ x["v_v"][b, h].astype(np.float64)
             assert np.abs(o[b, h, idx[b]] - ref).max() <= TOL_O["f32"]
             assert np.abs(lse[b, h, idx[b]] - ref_lse).max() <= TOL_LSE["f32"]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_attention_of_values_near_the_top_of_the_range(d):
+    """Weights are at most 1 before they are normalised too: one value of 2^125
+    among zeros gives its weight times itself.  Scores rise along the keys, by
+    less than the slack between two rescales."""
+    L, block = 700, 64
+    g = torch.Generator(device="cuda").manual_seed(d)
+    q, k = (torch.randn(1, 1, L, d, generator=g, device="cuda") for _ in range(2))
+    q[..., 0] = d**0.5
+    k[..., 0] = torch.arange(L, device="cuda") * (5.0 / L)  # 5 nats: 7.2 log2 units
+    v = torch.zeros(1, 1, L, d, device="cuda")
+    v[0, 0, L - 1] = 2.0**125
+    n_b = -(-L // block)
+    idx = torch.arange(n_b, dtype=torch.int32, device="cuda").expand(1, 1, n_b, n_b).contiguous()
+    cnt = torch.full((1, 1, n_b), n_b, dtype=torch.int32, device="cuda")
+    scale = float(np.float32(d**-0.5))
+    o, lse = sa.sa_sparse_attention(q, k, v, scale, block, idx, cnt, want_lse=True)
+    s = scale * (q[0, 0].double() @ k[0, 0].double().T.contiguous())
+    ref = torch.softmax(s, 1) @ v[0, 0].double()
+    assert ((o[0, 0].double() - ref).abs() <= 1e-5 * ref).all()
+    assert (lse[0, 0].double() - torch.logsumexp(s, 1)).abs().max() <= TOL_LSE["f32"]
