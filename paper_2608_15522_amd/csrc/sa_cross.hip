@@ -564,7 +564,7 @@ lse_combine_kernel(const float2* __restrict__ part, float* __restrict__ lse2, in
   __shared__ float2 red[kCombPhases][16];
   const int ph = threadIdx.x >> 4, jj = threadIdx.x & 15;
   const size_t n = static_cast<size_t>(P) * L_a;
-  const size_t t = static_cast<size_t>(blockIdx.x) * 16 + jj;
+  const size_t t = (static_cast<size_t>(blockIdx.z) * gridDim.x + blockIdx.x) * 16 + jj;
   // Every chunk counts, by its finite maximum (ph without a chunk: the lowest, and
   // a sum of 0): one whose sum is a NaN makes the value a NaN.
   float M = -FLT_MAX, S = 0.f;
@@ -1209,8 +1209,8 @@ void cross_bf16(const uint16_t* q_a, const uint16_t* k_v, const uint16_t* q_v,
   const int nchunk = ceil_div(L_v, ck);
   hipLaunchKernelGGL(a2v_lse_partial_kernel<D>, dim3(nchunk, nslab, P), dim3(kXNT), 0, s,
                      q_a, k_v, lse_part, L_v, L_a, nchunk, ck, c);
-  hipLaunchKernelGGL(lse_combine_kernel, dim3((nlse + 15) / 16), dim3(256), 0, s,
-                     lse_part, lse_a, P, L_a, nchunk);
+  hipLaunchKernelGGL(lse_combine_kernel, wide_grid((nlse + 15) / 16), dim3(256), 0, s, lse_part,
+                     lse_a, P, L_a, nchunk);
   column_masses<D>(q_a, k_v, q_v, k_a, lse_a, 1.f, nullptr, B, H, L_v, L_a, c, block, sal_v_tok,
                    sal_v_blk, sal_a_tok, accumulate, qbar, kbar, lay, ws, s);
 }

@@ -20,6 +20,15 @@ constexpr int kMaxPairs = 65535;  // largest B*H (a grid dimension indexes (b, h
 
 inline size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
+// Grid of n workgroups in x and z (y as given): a launch holds less than 2^32
+// threads in one dimension.  Workgroup blockIdx.z * gridDim.x + blockIdx.x; the
+// kernel leaves out those from n on.
+constexpr long kGridX = 1 << 16;
+inline dim3 wide_grid(long n, int y = 1) {
+  return dim3(static_cast<unsigned>(n < kGridX ? n : kGridX), y,
+              static_cast<unsigned>((n + kGridX - 1) / kGridX));
+}
+
 // Workspace of sa_cross_scores.  The bf16 path's parts; the fp32 path lays its
 // own out within the same total.
 struct CrossWs {

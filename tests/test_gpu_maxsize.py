@@ -65,3 +65,27 @@ def test_token_selection_at_maximum_length(values):
     ref_idx, ref_flag = oracle.select_protected_tokens(s, k)
     assert np.array_equal(idx.cpu().numpy(), ref_idx)
     assert np.array_equal(flag.cpu().numpy(), ref_flag)
+
+
+def _same_pairs(P, L_v, L_a, d, dtype):
+    """The same Q^a and K^v for every one of P heads, one batch item each."""
+    g = torch.Generator(device="cuda").manual_seed(L_v)
+    return [torch.randn(n, d, generator=g, device="cuda").to(dtype).expand(P, 1, n, d).contiguous()
+            for n in (L_a, L_v)]
+
+
+def _check_a2v(v_tok, q_a, k_v, scale, rel):
+    s = scale * (q_a[0, 0].double() @ k_v[0, 0].double().T.contiguous())
+    ref = torch.softmax(s, 1).sum(0) / s.shape[0]
+    for rows in v_tok.split(4096):
+        assert ((rows.double() - ref).abs() <= rel * ref).all()
+
+
+# Launches of more workgroups than one grid dimension holds threads for.
+def test_saliency_of_most_queries():
+    """65535 * 4097 log-sum-exps, 16 threads each, above 2^32 threads."""
+    P, L_a = 65535, 4097
+    print(f"case saliency P={P} L_a={L_a}", flush=True)
+    q_a, k_v = _same_pairs(P, 3, L_a, 64, torch.bfloat16)
+    v_tok = sa.sa_cross_scores(q_a, k_v, None, None, 0.125, 64)[0]
+    _check_a2v(v_tok, q_a, k_v, 0.125, 1e-4)
