@@ -760,8 +760,9 @@ v2a_colmass_kernel(const uint16_t* __restrict__ q_v,
 }
 
 // ---- finalize ---------------------------------------------------------------
-// Both directions' sums in one launch of 1024-thread workgroups.
-//  [0, B * n_b): sal_v_tok and sal_v_blk of one video block from the column
+// Both directions' sums in one launch of 1024-thread workgroups, batch item
+// blockIdx.y.
+//  blockIdx.x in [0, n_b): sal_v_tok and sal_v_blk of one video block from the column
 //    masses [B][H][L_v]: thread (ph, t) adds the heads ph, ph + NP, ... of
 //    token t in order (NP = 1024 / block phases), the phases are added in
 //    order, then the tokens by a tree.
@@ -771,14 +772,15 @@ constexpr int kFinThreads = 1024;
 constexpr int kFinAud = 16;  // audio tokens per workgroup
 __global__ void __launch_bounds__(kFinThreads)
 saliency_finalize_kernel(const float* __restrict__ colmass, float* __restrict__ sal_v_tok,
-                         float* __restrict__ sal_v_blk, int B, int H, int L_v, int block,
-                         float inv_norm_v, const float* __restrict__ v2a_part,
+                         float* __restrict__ sal_v_blk, int H, int L_v, int block, float inv_norm_v,
+                         const float* __restrict__ v2a_part,
                          float* __restrict__ sal_a_tok, int nparts, int L_a, float inv_norm_a,
                          int accumulate) {
   __shared__ float red[kFinThreads];
   const int tid = threadIdx.x, n_b = ceil_div(L_v, block);
-  if (static_cast<int>(blockIdx.x) < B * n_b) {
-    const int c = blockIdx.x % n_b, b = blockIdx.x / n_b;
+  const int b = blockIdx.y;
+  if (static_cast<int>(blockIdx.x) < n_b) {
+    const int c = blockIdx.x;
     const int NP = kFinThreads / block, ph = tid / block, t = tid % block;
     const int i = c * block + t;
     float v = 0.f;
@@ -807,8 +809,7 @@ saliency_finalize_kernel(const float* __restrict__ colmass, float* __restrict__ 
     }
     return;
   }
-  const int w = blockIdx.x - B * n_b, nat = ceil_div(L_a, kFinAud);
-  const int b = w / nat, j = (w % nat) * kFinAud + tid % kFinAud;
+  const int j = (static_cast<int>(blockIdx.x) - n_b) * kFinAud + tid % kFinAud;
   constexpr int NP = kFinThreads / kFinAud;
   const int ph = tid / kFinAud;
   float v = 0.f;
@@ -839,10 +840,10 @@ saliency_finalize_kernel(const float* __restrict__ colmass, float* __restrict__ 
 void launch_finalize(const float* colmass, float* sal_v_tok, float* sal_v_blk, int B, int H,
                      int L_v, int block, const float* v2a_part, float* sal_a_tok, int nchunk3,
                      int L_a, int accumulate, hipStream_t s) {
-  const int n_v = B * ceil_div(L_v, block);
-  const int n_a = sal_a_tok != nullptr ? B * ceil_div(L_a, kFinAud) : 0;
-  hipLaunchKernelGGL(saliency_finalize_kernel, dim3(n_v + n_a), dim3(kFinThreads), 0, s, colmass,
-                     sal_v_tok, sal_v_blk, B, H, L_v, block,
+  const int n_v = ceil_div(L_v, block);
+  const int n_a = sal_a_tok != nullptr ? ceil_div(L_a, kFinAud) : 0;
+  hipLaunchKernelGGL(saliency_finalize_kernel, dim3(n_v + n_a, B), dim3(kFinThreads), 0, s,
+                     colmass, sal_v_tok, sal_v_blk, H, L_v, block,
                      1.0f / (static_cast<float>(H) * static_cast<float>(L_a)), v2a_part, sal_a_tok,
                      H * nchunk3, L_a, 1.0f / (static_cast<float>(H) * static_cast<float>(L_v)),
                      accumulate);

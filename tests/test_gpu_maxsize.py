@@ -89,3 +89,14 @@ def test_saliency_of_most_queries():
     q_a, k_v = _same_pairs(P, 3, L_a, 64, torch.bfloat16)
     v_tok = sa.sa_cross_scores(q_a, k_v, None, None, 0.125, 64)[0]
     _check_a2v(v_tok, q_a, k_v, 0.125, 1e-4)
+
+
+def test_saliency_of_most_blocks():
+    """65535 batch items of 65 blocks, 1024 threads each, above 2^32 threads."""
+    B, L_v = 65535, 64 * 64 + 1
+    print(f"case saliency B={B} L_v={L_v}", flush=True)
+    q_a, k_v = _same_pairs(B, L_v, 3, 64, torch.bfloat16)
+    v_tok, v_blk, _ = sa.sa_cross_scores(q_a, k_v, None, None, 0.125, 64)
+    _check_a2v(v_tok, q_a, k_v, 0.125, 1e-4)
+    assert torch.equal(v_blk, v_blk[:1].expand_as(v_blk))
+    assert (v_blk[0].sum().double() - 1).abs() <= 1e-4
