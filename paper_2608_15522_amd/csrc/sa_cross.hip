@@ -761,8 +761,8 @@ v2a_colmass_kernel(const uint16_t* __restrict__ q_v,
 
 // ---- finalize ---------------------------------------------------------------
 // Both directions' sums in one launch of 1024-thread workgroups, batch item
-// blockIdx.y.
-//  blockIdx.x in [0, n_b): sal_v_tok and sal_v_blk of one video block from the column
+// blockIdx.y, workgroup w of its n_b + n_aud.
+//  w in [0, n_b): sal_v_tok and sal_v_blk of one video block from the column
 //    masses [B][H][L_v]: thread (ph, t) adds the heads ph, ph + NP, ... of
 //    token t in order (NP = 1024 / block phases), the phases are added in
 //    order, then the tokens by a tree.
@@ -773,14 +773,13 @@ constexpr int kFinAud = 16;  // audio tokens per workgroup
 __global__ void __launch_bounds__(kFinThreads)
 saliency_finalize_kernel(const float* __restrict__ colmass, float* __restrict__ sal_v_tok,
                          float* __restrict__ sal_v_blk, int H, int L_v, int block, float inv_norm_v,
-                         const float* __restrict__ v2a_part,
-                         float* __restrict__ sal_a_tok, int nparts, int L_a, float inv_norm_a,
-                         int accumulate) {
+                         const float* __restrict__ v2a_part, float* __restrict__ sal_a_tok,
+                         int nparts, int L_a, int n_aud, float inv_norm_a, int accumulate) {
   __shared__ float red[kFinThreads];
   const int tid = threadIdx.x, n_b = ceil_div(L_v, block);
-  const int b = blockIdx.y;
-  if (static_cast<int>(blockIdx.x) < n_b) {
-    const int c = blockIdx.x;
+  const int b = blockIdx.y, w = blockIdx.z * gridDim.x + blockIdx.x;
+  if (w < n_b) {
+    const int c = w;
     const int NP = kFinThreads / block, ph = tid / block, t = tid % block;
     const int i = c * block + t;
     float v = 0.f;
@@ -809,7 +808,8 @@ saliency_finalize_kernel(const float* __restrict__ colmass, float* __restrict__ 
     }
     return;
   }
-  const int j = (static_cast<int>(blockIdx.x) - n_b) * kFinAud + tid % kFinAud;
+  if (w - n_b >= n_aud) return;
+  const int j = (w - n_b) * kFinAud + tid % kFinAud;
   constexpr int NP = kFinThreads / kFinAud;
   const int ph = tid / kFinAud;
   float v = 0.f;
@@ -842,17 +842,17 @@ void launch_finalize(const float* colmass, float* sal_v_tok, float* sal_v_blk, i
                      int L_a, int accumulate, hipStream_t s) {
   const int n_v = ceil_div(L_v, block);
   const int n_a = sal_a_tok != nullptr ? ceil_div(L_a, kFinAud) : 0;
-  hipLaunchKernelGGL(saliency_finalize_kernel, dim3(n_v + n_a, B), dim3(kFinThreads), 0, s,
-                     colmass, sal_v_tok, sal_v_blk, H, L_v, block,
+  hipLaunchKernelGGL(saliency_finalize_kernel, wide_grid(static_cast<long>(n_v) + n_a, B),
+                     dim3(kFinThreads), 0, s, colmass, sal_v_tok, sal_v_blk, H, L_v, block,
                      1.0f / (static_cast<float>(H) * static_cast<float>(L_a)), v2a_part, sal_a_tok,
-                     H * nchunk3, L_a, 1.0f / (static_cast<float>(H) * static_cast<float>(L_v)),
+                     H * nchunk3, L_a, n_a, 1.0f / (static_cast<float>(H) * static_cast<float>(L_v)),
                      accumulate);
 }
 
 // ---- fp32 path --------------------------------------------------------------
 // Both passes form 16 x 16 score tiles with v_mfma_f32_16x16x4_f32, one
 // operand held in registers, the other streamed through LDS, and take both
-// directions in one launch (grid (a.n_wg + v.n_wg, P): the first a.n_wg
+// directions in one launch (a.n_wg + v.n_wg workgroups a pair: the first a.n_wg
 // workgroups of a pair serve a->v, the rest v->a), because either alone leaves
 // most of the chip idle at the sizes fp32 is used at.
 // Log-sum-exps: 16 queries a workgroup, whose waves share out the key tiles,
@@ -992,9 +992,11 @@ __global__ void __launch_bounds__(64 * kF32XWaves)
 row_lse2_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
   __shared__ __attribute__((aligned(1024))) char ring[kF32XWaves * 2 * RowTile16<D>::kBytes];
   __shared__ float2 red[kF32XWaves][16];
-  const bool second = static_cast<int>(blockIdx.x) >= a.n_wg;
+  const int w = blockIdx.z * gridDim.x + blockIdx.x;
+  if (w >= a.n_wg + v.n_wg) return;
+  const bool second = w >= a.n_wg;
   const F32Dir& p = second ? v : a;
-  const int wg = static_cast<int>(blockIdx.x) - (second ? a.n_wg : 0);
+  const int wg = w - (second ? a.n_wg : 0);
   const int nt = ceil_div(p.Lq, 16);
   const int qt = wg % nt, ch = wg / nt, pair = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1060,9 +1062,11 @@ colmass_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
   __shared__ __attribute__((aligned(1024))) char ring_lds[SPLIT * kRingBytes];
   __shared__ float red[SPLIT][kF32XRows];
   __shared__ __attribute__((aligned(16))) float lse_s[kF32XLse];
-  const bool second = static_cast<int>(blockIdx.x) >= a.n_wg;
+  const int w = blockIdx.z * gridDim.x + blockIdx.x;
+  if (w >= a.n_wg + v.n_wg) return;
+  const bool second = w >= a.n_wg;
   const F32Dir& p = second ? v : a;
-  const int wg = static_cast<int>(blockIdx.x) - (second ? a.n_wg : 0);
+  const int wg = w - (second ? a.n_wg : 0);
   const int Lq = p.Lq, Lk = p.Lk;
   const int nt = ceil_div(Lk, kF32XRows);
   const int kt = wg % nt, ch = wg / nt, pair = blockIdx.y;
@@ -1267,14 +1271,15 @@ void cross_f32(const float* q_a, const float* k_v, const float* q_v,
   F32Dir v{q_v, k_a, lse_v, v2a_part, L_v, L_a, 1, L_a, nchunk3, kV2aChunk, 0};
   a.n_wg = ceil_div(L_a, 16) * nlse;
   v.n_wg = rev ? ceil_div(L_v, 16) : 0;
-  hipLaunchKernelGGL(row_lse2_f32_kernel<D>, dim3(a.n_wg + v.n_wg, P), dim3(64 * kF32XWaves), 0, s, a,
-                     v, c);
+  hipLaunchKernelGGL(row_lse2_f32_kernel<D>, wide_grid(static_cast<long>(a.n_wg) + v.n_wg, P),
+                     dim3(64 * kF32XWaves), 0, s, a, v, c);
   // Column masses: a->v over all audio queries, v->a in chunks of 512 video
   // queries.
   a.n_wg = ceil_div(L_v, kF32XRows);
   v.n_wg = rev ? ceil_div(L_a, kF32XRows) * nchunk3 : 0;
-  const dim3 grid(a.n_wg + v.n_wg, P);
-  if (static_cast<long>(grid.x) * P <= kXcds * kCusPerXcd)
+  const long n_wg = static_cast<long>(a.n_wg) + v.n_wg;
+  const dim3 grid = wide_grid(n_wg, P);
+  if (n_wg * P <= kXcds * kCusPerXcd)
     hipLaunchKernelGGL((colmass_f32_kernel<D, 4>), grid, dim3(4 * 64 * kF32XWaves), 0, s, a, v, c);
   else
     hipLaunchKernelGGL((colmass_f32_kernel<D, 1>), grid, dim3(64 * kF32XWaves), 0, s, a, v, c);

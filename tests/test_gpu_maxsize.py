@@ -100,3 +100,24 @@ def test_saliency_of_most_blocks():
     _check_a2v(v_tok, q_a, k_v, 0.125, 1e-4)
     assert torch.equal(v_blk, v_blk[:1].expand_as(v_blk))
     assert (v_blk[0].sum().double() - 1).abs() <= 1e-4
+
+
+# fp32: more log-sum-exp, then more column-mass workgroups a pair than 65536, the
+# most that go in one grid dimension
+@pytest.mark.parametrize("L_v,L_a", [(200, 2**20 + 40), (262144, 8200)])
+def test_saliency_f32_of_many_workgroups(L_v, L_a):
+    print(f"case saliency f32 L_v={L_v} L_a={L_a}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(L_a)
+    q_a, k_v, q_v, k_a = (torch.randn(1, 1, n, 64, generator=g, device="cuda")
+                          for n in (L_a, L_v, L_v, L_a))
+    v_tok, _, a_tok = sa.sa_cross_scores(q_a, k_v, q_v, k_a, 0.125, 128)
+    for got, q, k in ((v_tok, q_a, k_v), (a_tok, q_v, k_a)):
+        q, k = q[0, 0].double(), k[0, 0].double().T.contiguous()
+        ref = torch.zeros(k.shape[1], dtype=torch.float64, device="cuda")
+        step = max(1, 2**27 // k.shape[1])
+        for i in range(0, q.shape[0], step):
+            ref += torch.softmax(0.125 * (q[i:i + step] @ k), 1).sum(0)
+        ref /= q.shape[0]
+        # sums of up to 2^18 positive terms a lane, rounded as they are added: their
+        # errors average out, 2^-24 * 2^9 bounds them by far
+        assert ((got[0].double() - ref).abs() <= 1e-4 * ref).all()
