@@ -229,12 +229,42 @@ __device__ __forceinline__ uint64_t desc_double_asc_index_key(double v,
   return (~ord & ~0xfffull) | idx;
 }
 
+// In-place ascending bitonic sort of n (a power of two) keys in LDS by the
+// whole workgroup.  Ends with a barrier.
+__device__ __forceinline__ void bitonic_sort_lds(uint64_t* keys, int n) {
+  const int tid = threadIdx.x;
+  const int nt = blockDim.x;
+  for (int size = 2; size <= n; size <<= 1) {
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      __syncthreads();
+      for (int t = tid; t < (n >> 1); t += nt) {
+        const int lo = 2 * t - (t & (stride - 1));
+        const int hi = lo + stride;
+        const bool up = (lo & size) == 0;
+        const uint64_t a = keys[lo];
+        const uint64_t b = keys[hi];
+        if ((a > b) == up) {
+          keys[lo] = b;
+          keys[hi] = a;
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
 __host__ __device__ constexpr int ceil_div(int a, int b) {
   return (a + b - 1) / b;
 }
 
 __host__ __device__ constexpr size_t align_to_8(size_t x) {
   return (x + 7) & ~static_cast<size_t>(7);
+}
+
+__host__ __device__ constexpr int next_pow2(int n) {
+  int p = 1;
+  while (p < n) p <<= 1;
+  return p;
 }
 
 }  // namespace sa

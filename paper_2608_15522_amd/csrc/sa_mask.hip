@@ -1,8 +1,9 @@
 // Protected selection and the protected block mask.
 //
 // K4 select_protected (Sec. 4.2, Eq. (8) at block granularity): every block's
-//    rank in its batch item by counting the smaller 64-bit keys (value
-//    descending, index ascending); the first k_prot are protected.
+//    rank in its batch item by the 64-bit keys (value descending, index
+//    ascending), by counting the smaller ones or, for many long items, by a
+//    bitonic sort in LDS; the first k_prot are protected.
 // K5 block_pool: per (b,h) and 1 to 8 consecutive blocks the mean of Q and of K
 //    over the valid tokens of each block, accumulated in fp64 (16-byte loads,
 //    fixed-order LDS reduction; the sums are exact, see block_pool_kernel),
@@ -24,13 +25,45 @@ namespace sa {
 namespace {
 
 // ---- K4 ---------------------------------------------------------------------
+// Two forms.  By counting: every block's rank is the number of smaller keys, n_b^2
+// compares a batch item, spread over the chip.  By sorting: one workgroup a batch
+// item, a chain of barriers but n_b log^2 n_b work.  Counting wins while the chip
+// has room (8 us at any n_b up to 8 items, sorting 8 to 21) and at any number of
+// items up to n_b = 256 (37 us against 60 at 4096 items); beyond, its work tells:
+// at n_b = 2048 16 items take 13 us against 21, 32 items 20 against 21, 64 items 35
+// against 21 and 4096 items 1888 against 203; at n_b = 600 128 items 9 against 15,
+// 512 items 25 against 18; at n_b = 400 512 items 13 against 13.
+inline bool rank_by_counting(int B, int n_b) {
+  return n_b <= 256 || static_cast<double>(B) * n_b * n_b <= 8e7;
+}
+
+__global__ void __launch_bounds__(1024)
+sort_protected_kernel(const float* __restrict__ sal_blk, int n_b, int k_prot, int n_pad,
+                      int32_t* __restrict__ prot_idx, uint8_t* __restrict__ prot_flag) {
+  __shared__ uint64_t keys[kMaxBlocks];
+  __shared__ uint8_t flag[kMaxBlocks];
+  const int b = blockIdx.x;
+  const float* s = sal_blk + static_cast<size_t>(b) * n_b;
+  for (int i = threadIdx.x; i < n_pad; i += blockDim.x) {
+    keys[i] = i < n_b ? desc_value_asc_index_key(s[i], static_cast<uint32_t>(i)) : ~0ull;
+    if (i < n_b) flag[i] = 0;
+  }
+  bitonic_sort_lds(keys, n_pad);
+  for (int i = threadIdx.x; i < k_prot; i += blockDim.x) {
+    const uint32_t c = static_cast<uint32_t>(keys[i] & 0xffffffffu);
+    flag[c] = 1;
+    if (prot_idx != nullptr) prot_idx[static_cast<size_t>(b) * k_prot + i] = c;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < n_b; i += blockDim.x)
+    prot_flag[static_cast<size_t>(b) * n_b + i] = flag[i];
+}
+
 // Grid (B, ceil(n_b / kSelBlocks)), 256 threads: B is bounded by nothing else, and
 // only the first grid dimension goes beyond 65535.  Every workgroup holds the
 // batch item's keys in LDS and ranks kSelBlocks of its blocks: kSelParts
 // threads per block each count the smaller keys in an eighth of the list, and
-// the rank (keys are distinct) places the block.  No barrier chain: 36 bitonic
-// steps of one 1024-thread workgroup took 7.4 us at n_b = 256, two batch
-// items of n_b = 141 took 14.
+// the rank (keys are distinct) places the block.
 constexpr int kSelParts = 8;
 constexpr int kSelBlocks = 256 / kSelParts;
 __global__ void __launch_bounds__(256)
@@ -438,8 +471,12 @@ void launch_mask_build(int E, dim3 grid, hipStream_t s, const double* qbar,
 void launch_select_protected(const float* sal_blk, int B, int n_b, int k_prot,
                              int32_t* prot_idx, uint8_t* prot_flag,
                              hipStream_t s) {
-  hipLaunchKernelGGL(select_protected_kernel, dim3(B, ceil_div(n_b, kSelBlocks)), dim3(256), 0, s,
-                     sal_blk, n_b, k_prot, prot_idx, prot_flag);
+  if (rank_by_counting(B, n_b))
+    hipLaunchKernelGGL(select_protected_kernel, dim3(B, ceil_div(n_b, kSelBlocks)), dim3(256), 0, s,
+                       sal_blk, n_b, k_prot, prot_idx, prot_flag);
+  else
+    hipLaunchKernelGGL(sort_protected_kernel, dim3(B), dim3(1024), 0, s, sal_blk, n_b, k_prot,
+                       next_pow2(n_b), prot_idx, prot_flag);
 }
 
 template <typename T, int D>

@@ -31,10 +31,11 @@ def test_block_ranking(n_b):
             assert np.array_equal(flag[b].cpu().numpy(), ref)
 
 
-# more batch items than the second and third grid dimensions hold
-@pytest.mark.parametrize("n_b", [1, 40])
-def test_block_ranking_of_many_items(n_b):
-    B = 65536 + 7
+# more batch items than the second and third grid dimensions hold; ranks by sorting
+# (many long items), and by counting just below that line
+@pytest.mark.parametrize("B,n_b", [(65536 + 7, 1), (65536 + 7, 40), (1217, 257), (1210, 257),
+                                   (20, 2048), (19, 2047), (600, 401)])
+def test_block_ranking_of_many_items(B, n_b):
     print(f"case ranking B={B} n_b={n_b}", flush=True)
     s = _randn(B, n_b, seed=n_b, dtype=torch.float32).round_(decimals=1)  # ties
     k = (n_b + 2) // 3
