@@ -117,6 +117,34 @@ select_tokens_kernel(const float* __restrict__ sal, int L, int k_tok,
     });
   };
 
+  auto first_lane = [](uint64_t m) { return __ffsll(static_cast<unsigned long long>(m)) - 1; };
+  // Whether the wave's keys share their digits so much that adding them one by one
+  // would serialise (the LDS takes a wave's adds to one address in turn): judged by
+  // the first and the middle 64 of them, as runs of equal saliencies (a floor, zeros)
+  // are what makes them so.  At 32760 tokens a constant map but for one token took
+  // 136 us without this and 50 with it (two bits a step: 99), a floor under 90 % of
+  // the tokens 125 and 51 (89), and a saliency map 26.7 and 27.1.  One wave's adds
+  // (up to 512 tokens) are faster one by one (8 us against 11), and keys read again
+  // from memory on every pass stay ahead of two bits a step without it (277 against
+  // 300 at 65536).
+  auto crowded = [&](auto counts, auto digit) {
+    if constexpr (R > 0 && NW > 1) {
+      int most = 0;
+#pragma unroll
+      for (int j = 0; j < R; j += R / 2) {
+        const bool in = w0 + 64 * j + lane < w1 && counts(vk[j]);
+        const uint64_t m = __ballot(in);
+        if (m == 0) continue;
+        const uint32_t d = digit(vk[j]);
+        const uint32_t d0 = __builtin_amdgcn_readlane(d, first_lane(m));
+        most = max(most, static_cast<int>(__popcll(__ballot(in && d == d0))));
+      }
+      return most >= 32;
+    } else {
+      return false;
+    }
+  };
+
   // Search for T, for 0 < k_tok < L.  `fixed` marks the decided bits of T,
   // `prefix` their values; `below` keys lie under the prefix group and
   // `size` keys share it.  k_tok == L keeps every token, k_tok == 0 none.
@@ -149,9 +177,25 @@ select_tokens_kernel(const float* __restrict__ sal, int L, int k_tok,
       const uint32_t digit_mask = (2u << (hb - lo)) - 1u;
       for (int i = tid; i < kDigits; i += NT) hist[i] = 0u;
       __syncthreads();
-      for_keys([&](uint32_t key) {
-        if ((key & fixed) == prefix) atomicAdd(&hist[(key >> lo) & digit_mask], 1u);
-      });
+      auto counts = [&](uint32_t key) { return (key & fixed) == prefix; };
+      auto digit = [&](uint32_t key) { return (key >> lo) & digit_mask; };
+      if (crowded(counts, digit)) {
+        // one add for the keys that share the digit of the wave's first one
+        for_all([&](uint32_t key, int, bool ok) {
+          const bool in = ok && counts(key);
+          const uint64_t m = __ballot(in);
+          if (m == 0) return;
+          const uint32_t d = digit(key);
+          const uint32_t d0 = __builtin_amdgcn_readlane(d, first_lane(m));
+          const uint64_t same = __ballot(in && d == d0);
+          if (in && d != d0) atomicAdd(&hist[d], 1u);
+          if (lane == 0) atomicAdd(&hist[d0], static_cast<uint32_t>(__popcll(same)));
+        });
+      } else {
+        for_keys([&](uint32_t key) {
+          if (counts(key)) atomicAdd(&hist[digit(key)], 1u);
+        });
+      }
       __syncthreads();
       if (wave == 0) {
         // the digit that holds the k_tok-th key, in the lane of its four

@@ -201,16 +201,19 @@ def test_saliency_f32_chunks(H, L_v, L_a, d):
 
 
 # token selection by digits of eight bits: both sides of every register form,
-# keys that differ in the last bits only, in the sign, in few values, in none
+# keys that differ in the last bits only, in the sign, in few values, in none, in
+# few tokens (a wave's keys that share their digits are added together)
 @pytest.mark.parametrize("L", [1, 65, 512, 513, 4096, 4097, 16385, 32768, 32769, 70001])
-@pytest.mark.parametrize("kind", ["map", "adjacent", "signs", "few", "equal"])
+@pytest.mark.parametrize("kind", ["map", "adjacent", "signs", "few", "equal", "floor", "one"])
 def test_token_selection_digits(L, kind):
     rng = np.random.default_rng(L)
     s = {"map": np.exp(rng.standard_normal((2, L))),
          "adjacent": (np.float32(1.0).view(np.int32) + rng.integers(0, 300, (2, L))).astype(np.int32)
          .view(np.float32),
          "signs": rng.standard_normal((2, L)) * 10.0 ** rng.integers(-30, 30, (2, L)),
-         "few": rng.integers(-2, 3, (2, L)) * 0.25, "equal": np.full((2, L), 0.5)}[kind]
+         "few": rng.integers(-2, 3, (2, L)) * 0.25, "equal": np.full((2, L), 0.5),
+         "floor": np.where(np.arange(L) % 97 < L % 97, rng.random((2, L)), 1e-3),
+         "one": np.where(np.arange(L) == L // 2, 2.0, np.full((2, L), 0.5))}[kind]
     s = s.astype(np.float32)
     for k in sorted({1, max(1, L // 20), max(1, L - 1)}):
         idx, flag = sa.sa_select_protected_tokens(torch.from_numpy(s).cuda(), k)
