@@ -5,6 +5,7 @@
 #include <stdarg.h>
 #include <stdio.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 
@@ -17,7 +18,9 @@
 // the launch lists (AttnWs::min, which bounds what the call accepts) there is
 // room for the runs of any split_rows call (AttnWs::starts and part).
 constexpr size_t kStaticScratchBytes = static_cast<size_t>(4) << 20;
-constexpr size_t kStaticSplitBytes = static_cast<size_t>(66) << 20;
+constexpr size_t kStaticSplitBytes =
+    std::max({sa::attn_split_bytes(128, 128), sa::attn_split_bytes(128, 64),
+              sa::attn_split_bytes(64, 128), sa::attn_split_bytes(64, 64)});
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticSplitBytes];
 
 namespace {
@@ -130,8 +133,7 @@ void launch_sparse_attention(const void* q, const void* k, const void* v, void* 
                              size_t ws_bytes, hipStream_t s) {
   const sa::AttnWs lay = sa::attn_ws_layout(B, H, sa::ceil_div(L, block), d, block);
   if (dtype == SA_BF16) {
-    const bool split = lay.total > lay.min && ws_bytes >= lay.total &&
-                       &sa::launch_sparse_attention_split_bf16 != nullptr;
+    const bool split = lay.total > lay.min && ws_bytes >= lay.total;
     (split ? sa::launch_sparse_attention_split_bf16 : sa::launch_sparse_attention_bf16)(
         static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
         static_cast<const uint16_t*>(v), static_cast<uint16_t*>(o), lse, B, H, L, d,

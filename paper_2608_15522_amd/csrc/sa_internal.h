@@ -18,7 +18,7 @@ constexpr int kV2aChunk = 512;    // video queries per v->a workgroup
 constexpr int kMaxBlocks = 2048;  // largest supported n_b
 constexpr int kMaxPairs = 65535;  // largest B*H (a grid dimension indexes (b, h))
 
-inline size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
+constexpr size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Grid of n workgroups in x and z (y as given): a launch holds less than 2^32
 // threads in one dimension.  Workgroup blockIdx.z * gridDim.x + blockIdx.x; the
@@ -89,7 +89,7 @@ constexpr int kXcds = 8, kCusPerXcd = 32;  // MI355X
 // bf16 sparse attention: workgroups that the chip holds at once, two of 4 waves
 // (256 VGPRs a wave) a CU, or of 2 waves two (d = 128: 68 KB of LDS each) or
 // four.
-inline int attn_slots(int d, int block) {
+constexpr int attn_slots(int d, int block) {
   return kXcds * kCusPerXcd * (block == 64 && d == 64 ? 4 : 2);
 }
 // Whether the lists may be cut into one equal run per slot (the schedule kernel
@@ -110,6 +110,16 @@ struct AttnWs {
   size_t total;
 };
 
+constexpr size_t attn_starts_bytes(int d, int block) {
+  return align_up(8 * (static_cast<size_t>(attn_slots(d, block)) + 2));
+}
+// `starts` and `part` of a call that may cut its lists.
+constexpr size_t attn_split_bytes(int d, int block) {
+  return attn_starts_bytes(d, block) +
+         align_up(2 * static_cast<size_t>(attn_slots(d, block)) * block *
+                  (static_cast<size_t>(d) * 4 + 8));
+}
+
 // The lists take half of what `min` has room for: that size is kept, since it
 // also bounds what sa_sparse_attention_noalloc accepts.
 inline AttnWs attn_ws_layout(int B, int H, int n_b, int d, int block) {
@@ -118,14 +128,11 @@ inline AttnWs attn_ws_layout(int B, int H, int n_b, int d, int block) {
   w.sched = off; off += 2 * align_up(sizeof(int32_t) * B * H * n_b);
   w.claim = off; off += align_up(sizeof(int32_t) * 8 * 64);
   w.min = off;
-  w.starts = w.part = off;
+  w.starts = w.part = w.total = off;
   if (split_rows(B * H, n_b, d, block)) {
-    const size_t slots = attn_slots(d, block);
-    off += align_up(8 * (slots + 2));
-    w.part = off;
-    off += align_up(2 * slots * block * (static_cast<size_t>(d) * 4 + 8));
+    w.part = off + attn_starts_bytes(d, block);
+    w.total = off + attn_split_bytes(d, block);
   }
-  w.total = off;
   return w;
 }
 
@@ -243,12 +250,11 @@ void launch_sparse_attention_bf16(const uint16_t* q, const uint16_t* k,
                                   const int32_t* kv_cnt, char* ws,
                                   hipStream_t s);
 // The same with the lists cut into one run per slot (split_rows): ws holds
-// attn_ws_layout's total.  Weak: a host-only build of the C ABI links without
-// it and then does not split.
-__attribute__((weak)) void launch_sparse_attention_split_bf16(
-    const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* o, float* lse, int B, int H,
-    int L, int d, float scale, int block, const int32_t* kv_idx, const int32_t* kv_cnt, char* ws,
-    hipStream_t s);
+// attn_ws_layout's total.
+void launch_sparse_attention_split_bf16(const uint16_t* q, const uint16_t* k, const uint16_t* v,
+                                        uint16_t* o, float* lse, int B, int H, int L, int d,
+                                        float scale, int block, const int32_t* kv_idx,
+                                        const int32_t* kv_cnt, char* ws, hipStream_t s);
 void launch_sparse_attention_f32(const float* q, const float* k,
                                  const float* v, float* o, float* lse, int B,
                                  int H, int L, int d, float scale, int block,

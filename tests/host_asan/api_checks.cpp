@@ -5,10 +5,12 @@
 // Reads one case per line on stdin:
 //   call <name> <expected rc> <needle in hex, "-" for none> <args...>
 //   ws <call> <B> <H> <L_v> <L_a> <d> <block>
+//   route <name> <args...>
 // Arguments are integers (pointers as addresses, NULL as 0) or floats, in
 // the order of the C signature.  For a "call" case it checks the return
 // code, that sa_last_error() holds the needle, and that a rejected call
-// reached no launcher; for "ws" it prints the size.  Exit status 0 iff every
+// reached no launcher; for "ws" it prints the size, for "route" the launchers
+// that the call reached ("none", "plain" or "split").  Exit status 0 iff every
 // case passed (a sanitizer report aborts the process).
 #include <cstdint>
 #include <cstdio>
@@ -21,7 +23,7 @@
 
 #include "sa.h"
 
-extern "C" int sa_host_stub_launches;
+extern "C" int sa_host_stub_launches, sa_host_stub_splits;
 
 namespace {
 
@@ -141,6 +143,15 @@ int main() {
     if (tok.empty()) continue;
     if (tok[0] == "ws" && tok.size() == 8) {
       std::printf("ws %zu\n", sa_workspace_size(I(1), I(2), I(3), I(4), I(5), I(6), I(7)));
+      continue;
+    }
+    if (tok[0] == "route" && tok.size() > 2) {
+      const int launches = sa_host_stub_launches, splits = sa_host_stub_splits;
+      int rc = -1;
+      if (!dispatch(tok[1], 2, &rc)) return 2;
+      std::printf("route %s\n", sa_host_stub_launches == launches ? "none"
+                                : sa_host_stub_splits == splits   ? "plain"
+                                                                  : "split");
       continue;
     }
     if (tok[0] != "call" || tok.size() < 4) {

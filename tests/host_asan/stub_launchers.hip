@@ -6,6 +6,7 @@
 #include "../../paper_2608_15522_amd/csrc/sa_internal.h"
 
 extern "C" int sa_host_stub_launches = 0;
+extern "C" int sa_host_stub_splits = 0;  // those of the launcher that may cut lists
 
 namespace sa {
 
@@ -49,6 +50,12 @@ void launch_mask_from_means(const double*, const double*, int, int, int, int, fl
 void launch_sparse_attention_bf16(const uint16_t*, const uint16_t*, const uint16_t*, uint16_t*,
                                   float*, int, int, int, int, float, int, const int32_t*,
                                   const int32_t*, char*, hipStream_t) SA_STUB()
+void launch_sparse_attention_split_bf16(const uint16_t*, const uint16_t*, const uint16_t*,
+                                        uint16_t*, float*, int, int, int, int, float, int,
+                                        const int32_t*, const int32_t*, char*, hipStream_t) {
+  ++sa_host_stub_launches;
+  ++sa_host_stub_splits;
+}
 void launch_sparse_attention_f32(const float*, const float*, const float*, float*, float*, int,
                                  int, int, int, float, int, const int32_t*, const int32_t*,
                                  char*, hipStream_t) SA_STUB()

@@ -92,6 +92,31 @@ def test_valid_calls_reach_the_launchers_under_sanitizers(checker):
             assert "rc 4 (want 0)" in ln and "launched 1" in ln, ln
 
 
+@pytest.mark.parametrize("B,H,L,d,block", [
+    (1, 3, 32760, 128, 128), (1, 1, 4096, 128, 64), (1, 2, 12000, 64, 128), (1, 10, 18002, 64, 64)])
+def test_sparse_attention_route_by_workspace(checker, B, H, L, d, block):
+    """Lists may be cut where the workspace has room for the partial rows; down
+    to the least size they are not, and below it nothing is launched.  fp32 calls
+    and calls of many rows have the least size only."""
+    n_b = -(-L // block)
+    least = 2 * -(-4 * B * H * n_b // 256) * 256 + 2048
+    total = sa.sa_workspace_size(sa.SA_CALL_SPARSE_ATTENTION, B, H, L, 1, d, block)
+    assert total > least
+
+    def route(**kw):
+        kw = {**dict(B=B, H=H, L=L, d=d, block=block, dtype=0), **kw}
+        return "route sa_sparse_attention " + " ".join(_arg(v) for v in _attn.args(**kw))
+
+    cases = [(dict(ws_bytes=total), "split"), (dict(ws_bytes=2**40), "split"),
+             (dict(ws_bytes=total - 1), "plain"), (dict(ws_bytes=least), "plain"),
+             (dict(ws_bytes=least - 1), "none"), (dict(ws_bytes=total, dtype=1), "plain"),
+             (dict(ws_bytes=2**40, H=4096), "plain"), (dict(ws_bytes=2**40, L=64), "plain")]
+    res = _run(checker, [route(**kw) for kw, _ in cases])
+    assert res.returncode == 0, res.stdout[-3000:] + res.stderr[-3000:]
+    got = [ln.split()[1] for ln in res.stdout.splitlines() if ln.startswith("route ")]
+    assert got == [want for _, want in cases], res.stdout
+
+
 SIZES = [(c, B, H, L_v, L_a, d, blk)
          for c in range(7)
          for (B, H, L_v, L_a, d, blk) in [
