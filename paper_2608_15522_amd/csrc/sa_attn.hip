@@ -20,11 +20,12 @@
 // only when a lane's max grows by more than 2^8.  Keys past L are -inf, rows
 // past L are never written.
 //
-// Rows beyond what the chip holds at once go through a launch schedule: each
+// Rows go through a launch schedule: each
 // XCD takes every 8th (batch, head) pair, first the full rows of all its pairs
 // (protected rows hold the full list), then the other rows one pair at a time,
 // so that a pair's K/V blocks are shared through one XCD's L2 and the long full
-// rows do not run alone at the end of the launch.  Calls of few rows may cut
+// rows do not run alone at the end of the launch.  Small calls and short pairs go
+// out directly, one workgroup a row (direct_rows).  Calls of few rows may cut
 // the rows' lists into equal runs instead, and merge the rows that runs share.
 //
 // Gather form: dense rows gathered by index (protected tokens) or all rows
@@ -141,7 +142,7 @@ __global__ void __launch_bounds__(1024)
 schedule_rows_kernel(const int32_t* __restrict__ kv_cnt, int32_t* __restrict__ sched,
                      int* __restrict__ claim, int P, int n_b, int2* __restrict__ starts, int slots) {
   __shared__ int full_before[kMaxPairs / kXcds + 2];  // full rows of the list's earlier pairs
-  if (blockIdx.x == kXcds) {
+  if (sched == nullptr || blockIdx.x == kXcds) {
     cut_rows(kv_cnt, starts, slots, P * n_b, n_b);
     return;
   }
@@ -214,6 +215,29 @@ schedule_rows_kernel(const int32_t* __restrict__ kv_cnt, int32_t* __restrict__ s
       if (r < n_b) out[pos] = (pair << 11) | r;
     }
   }
+}
+
+// The rank-th query block of a pair in the order full lists (protected query
+// blocks, n_b / k_keep times as long as the others), then the rest, by index;
+// every wave finds it by ballots.
+__device__ __forceinline__ int full_first_row(const int32_t* __restrict__ cnts, int n_b, int rank) {
+  const int lane = threadIdx.x & 63;
+  int nfull = 0;
+  for (int i0 = 0; i0 < n_b; i0 += 64)
+    nfull += __popcll(__ballot(i0 + lane < n_b && cnts[min(i0 + lane, n_b - 1)] >= n_b));
+  const bool want_full = rank < nfull;
+  int skip = want_full ? rank : rank - nfull;
+  for (int i0 = 0; i0 < n_b; i0 += 64) {
+    uint64_t m = __ballot(i0 + lane < n_b &&
+                          (cnts[min(i0 + lane, n_b - 1)] >= n_b) == want_full);
+    const int c64 = __popcll(m);
+    if (skip < c64) {
+      for (; skip > 0; --skip) m &= m - 1;
+      return __builtin_amdgcn_readfirstlane(i0 + __ffsll(static_cast<unsigned long long>(m)) - 1);
+    }
+    skip -= c64;
+  }
+  return 0;
 }
 
 typedef __attribute__((address_space(3))) uint16_t lds_u16_t;
@@ -295,7 +319,9 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
   // evens out XCDs that run at different speeds or own fewer pairs (an XCD
   // without a pair of its own starts at list x % P).  Each row is computed the
   // same way whichever workgroup takes it.  Otherwise there is one workgroup
-  // per row (dense rows: XCD-major over pairs).
+  // per row: full rows of every pair first (direct_rows; one more dependent load,
+  // against the claim and the list of a persistent workgroup), or, for dense rows,
+  // XCD-major over pairs.
   const bool runs =
       SPLIT && __builtin_amdgcn_readfirstlane(starts[static_cast<int>(gridDim.x) + 1].x) != 0;
   const bool persistent = !GATHER && !runs && sched != nullptr;
@@ -350,6 +376,14 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
     } else {
       pair = blockIdx.x % P;
       rank = blockIdx.x / P;
+      if (SPLIT && rank >= n_b) break;  // one workgroup per slot, fewer rows
+      if constexpr (!GATHER) {
+        // in index order two full rows may share a CU, or start last (1.2 times as
+        // long); at most one row a CU, the order is the same to all
+        r = P * n_b > kXcds * kCusPerXcd
+                ? full_first_row(kv_cnt + static_cast<size_t>(pair) * n_b, n_b, rank)
+                : rank;
+      }
     }
   }
   const size_t row_base = static_cast<size_t>(pair) * n_b;
@@ -363,7 +397,6 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
     kb0 = n_b * split / n_split;
     cnt = n_b * (split + 1) / n_split - kb0;
   } else {
-    if (!persistent && !runs) r = rank;
     cnt = kv_cnt[row_base + r];
     cnt = cnt < 0 ? 0 : (cnt > n_b ? n_b : cnt);
     idx = kv_idx + (row_base + r) * n_b;
@@ -1019,30 +1052,11 @@ sparse_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
   int row0 = blockIdx.y * kF32Rows;
 
   if constexpr (!GATHER) {
-    // Row tiles of full lists (protected query blocks) take n_b / k_keep
-    // times as long as the others and start first: workgroup y of a pair
-    // takes row tile y % per_block of the (y / per_block)-th block in the
-    // order full lists, then the rest (every wave finds it by ballots).
+    // Row tiles of full lists start first: workgroup y of a pair takes row tile
+    // y % per_block of the (y / per_block)-th block in that order.
     const int per_block = block / kF32Rows;
-    const int slot = blockIdx.y / per_block;
-    const int32_t* cnts = kv_cnt + static_cast<size_t>(pair) * n_b;
-    int nfull = 0;
-    for (int i0 = 0; i0 < n_b; i0 += 64)
-      nfull += __popcll(__ballot(i0 + lane < n_b && cnts[i0 + lane] >= n_b));
-    const bool want_full = slot < nfull;
-    int skip = want_full ? slot : slot - nfull, r = 0;
-    for (int i0 = 0; i0 < n_b; i0 += 64) {
-      const bool in = i0 + lane < n_b;
-      uint64_t m = __ballot(in && (cnts[min(i0 + lane, n_b - 1)] >= n_b) == want_full);
-      const int c64 = __popcll(m);
-      if (skip < c64) {
-        for (; skip > 0; --skip) m &= m - 1;
-        r = i0 + __ffsll(static_cast<unsigned long long>(m)) - 1;
-        break;
-      }
-      skip -= c64;
-    }
-    r = __builtin_amdgcn_readfirstlane(r);
+    const int r = full_first_row(kv_cnt + static_cast<size_t>(pair) * n_b, n_b,
+                                 blockIdx.y / per_block);
     row0 = r * block + (blockIdx.y % per_block) * kF32Rows;
     if (row0 >= L) return;  // row tiles of the last block past the last token
     // the list's valid entries (wave 0), in list order
@@ -1245,13 +1259,16 @@ static void sparse_attention_bf16(const uint16_t* q, const uint16_t* k, const ui
   const float c = scale * kLog2e;
   const int slots = attn_slots(D, BLOCK);
   const int rows = P * n_b;
+  // a call that may cut its lists has a workgroup per slot, so that only as many
+  // rows go out directly
+  const bool direct = split ? rows <= slots : direct_rows(P, n_b, D, BLOCK);
+  int32_t* sched = direct ? nullptr : reinterpret_cast<int32_t*>(ws + lay.sched);
+  int* claim = direct ? nullptr : reinterpret_cast<int*>(ws + lay.claim);
   if (split) {
     int2* starts = reinterpret_cast<int2*>(ws + lay.starts);
     float* part = reinterpret_cast<float*>(ws + lay.part);
-    int32_t* sched = reinterpret_cast<int32_t*>(ws + lay.sched);
-    int* claim = reinterpret_cast<int*>(ws + lay.claim);
-    hipLaunchKernelGGL(schedule_rows_kernel, dim3(kXcds + 1), dim3(1024), 0, s, kv_cnt, sched,
-                       claim, P, n_b, starts, slots);
+    hipLaunchKernelGGL(schedule_rows_kernel, dim3(direct ? 1 : kXcds + 1), dim3(1024), 0, s, kv_cnt,
+                       sched, claim, P, n_b, starts, slots);
     hipLaunchKernelGGL((sparse_attn_bf16_kernel<D, BLOCK, Rows::kSplit>), dim3(slots),
                        dim3(2 * BLOCK), 0, s, q, k, v, o, lse, kv_idx, kv_cnt, sched, claim, P, L,
                        n_b, c, nullptr, 0, H, 1, part, L, starts);
@@ -1259,18 +1276,12 @@ static void sparse_attention_bf16(const uint16_t* q, const uint16_t* k, const ui
                        part, starts, n_b, L, o, lse);
     return;
   }
-  int32_t* sched = nullptr;
-  int* claim = nullptr;
-  // Rows that all run at once need no schedule.
-  if (rows > slots) {
-    sched = reinterpret_cast<int32_t*>(ws + lay.sched);
-    claim = reinterpret_cast<int*>(ws + lay.claim);
+  if (!direct)
     hipLaunchKernelGGL(schedule_rows_kernel, dim3(kXcds), dim3(1024), 0, s, kv_cnt, sched, claim, P,
                        n_b, nullptr, 0);
-  }
   hipLaunchKernelGGL((sparse_attn_bf16_kernel<D, BLOCK, Rows::kList>),
-                     dim3(sched != nullptr ? slots : rows), dim3(2 * BLOCK), 0, s, q, k, v, o, lse,
-                     kv_idx, kv_cnt, sched, claim, P, L, n_b, c, nullptr, 0, H, 1, nullptr, L,
+                     dim3(direct ? rows : slots), dim3(2 * BLOCK), 0, s, q, k, v, o,
+                     lse, kv_idx, kv_cnt, sched, claim, P, L, n_b, c, nullptr, 0, H, 1, nullptr, L,
                      nullptr);
 }
 

@@ -92,6 +92,21 @@ constexpr int kXcds = 8, kCusPerXcd = 32;  // MI355X
 constexpr int attn_slots(int d, int block) {
   return kXcds * kCusPerXcd * (block == 64 && d == 64 ? 4 : 2);
 }
+// Whether rows go out one workgroup each, full rows of every pair first, without
+// the schedule kernel and the claims of its lists (about 10 us in all, and 1.5 us a
+// 128 pairs): rows that all run at once; pairs whose K and V take at most 256 KB,
+// which gain nothing from one XCD's L2; and small calls, by the multiply-adds of
+// their dense Q K^T.  Over some 4400 calls of 5 to 63 blocks a pair, densities of
+// 0.1 to 0.5 and 0 to 10 % full rows this is 0.87 of the time of heaviest rows first
+// by a ranking kernel (95 % of them at most 0.98, where the schedule took up to 1.5
+// times as long below 2^33 multiply-adds and 1.1 up to 2^34); above 2^36 the
+// schedule takes 0.82 of that time and this 0.97.
+inline bool direct_rows(int P, int n_b, int d, int block) {
+  const long long rows = static_cast<long long>(P) * n_b;
+  return rows <= attn_slots(d, block) || n_b * block * d <= 65536 ||
+         rows * n_b * block * block * d <= 1ll << 34;
+}
+
 // Whether the lists may be cut into one equal run per slot (the schedule kernel
 // decides, from the lists' lengths): with more than four rows a slot, or lists
 // of less than 64 blocks, whole rows were at least as fast at every density

@@ -94,11 +94,13 @@ def test_saliency_chunks(H, L_v, L_a, d):
             assert ((x[0].double() - ref).abs() <= SAL_REL * ref + SAL_ABS).all()
 
 
-# pair counts that are no multiple of 8, fewer than 8, and a multiple; rows on
-# both sides of what the chip holds at once; lists of every length
+# pair counts that are no multiple of 8, fewer than 8, and a multiple; lists of
+# every length; rows that go out directly (at most one a CU, at most what the chip
+# holds at once, short pairs, a small call) and by the schedule
 @pytest.mark.parametrize("H,n_b,tail,d,block", [
     (3, 20, 7, 128, 128), (5, 110, 128, 128, 128), (12, 87, 50, 64, 64), (8, 65, 1, 64, 128),
-    (1, 600, 64, 128, 64), (17, 31, 64, 128, 64)])
+    (1, 600, 64, 128, 64), (17, 31, 64, 128, 64), (20, 25, 7, 128, 64), (16, 63, 1, 64, 64),
+    (700, 4, 30, 64, 64), (40, 33, 9, 128, 128), (71, 61, 5, 64, 64)])
 def test_sparse_attention_schedule(H, n_b, tail, d, block):
     L = (n_b - 1) * block + tail
     print(f"case schedule H={H} n_b={n_b} tail={tail} d={d} block={block}", flush=True)
