@@ -12,6 +12,7 @@
 // hardware gives the k values inside a lane.
 #pragma once
 
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -51,21 +52,20 @@ __device__ __forceinline__ f32x4 ldg_f32x4(const float* p) {
 }
 
 // scale * log2(e) as an fp32 pair: the product's own rounding (2^-24 of it with
-// one fp32 factor) drops out of a score.
+// one fp32 factor) drops out of a score.  lo > 0, so that both parts of a score of
+// -inf are -inf (-inf * hi - inf * lo would be a NaN for lo < 0, and for lo = 0).
 struct Log2Scale {
   float hi, lo;
 };
 // c * s - ref in two FMAs, good to an ulp of the larger of ref and the result.
-// s = -inf takes no low part: lo is negative for some scales (d = 128), and
-// -inf * lo + -inf * hi would be a NaN where the weight is 0.
 __device__ __forceinline__ float log2_score(float s, Log2Scale c, float ref) {
-  const float t = s == -INFINITY ? 0.f : s;
-  return fmaf(s, c.hi, fmaf(t, c.lo, -ref));
+  return fmaf(s, c.hi, fmaf(s, c.lo, -ref));
 }
 inline Log2Scale log2_scale(float scale) {
   const double c = static_cast<double>(scale) * 1.4426950408889634;
-  const float hi = static_cast<float>(c);
-  return {hi, static_cast<float>(c - static_cast<double>(hi))};
+  float hi = static_cast<float>(c);
+  if (static_cast<double>(hi) >= c) hi = nextafterf(hi, 0.f);
+  return {hi, fmaxf(static_cast<float>(c - static_cast<double>(hi)), FLT_MIN)};
 }
 
 __device__ __forceinline__ f32x16 zero16() {

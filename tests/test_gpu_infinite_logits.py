@@ -104,6 +104,17 @@ def test_saliency_f32(seg, L_a, d):
     _check_saliency(L_a, d, seg, torch.float32, 1e-5)
 
 
+# scales whose fp32 product with log2(e) is above and below the exact one
+@pytest.mark.parametrize("scale", [1.0, 0.5, 0.3, 0.1, 0.07, 0.044194174, 0.01, 1e-6])
+def test_saliency_f32_of_any_scale(scale):
+    print(f"case -inf saliency f32 scale={scale}", flush=True)
+    q, k, _, _, _ = _masked_inputs(1, 40, 64, "mid", torch.float32)
+    ref = torch.softmax(torch.tensor(scale).double() * (q[0, 0].double() @ k[0, 0].double().T.contiguous()), 1)
+    got = sa.sa_cross_scores(q, k, None, None, scale, 64)[0][0].double()
+    # logits of up to 40: 2^-24 * 40 of a weight, thrice
+    assert ((got - ref.sum(0) / 40).abs() <= 1e-5 * ref.sum(0) / 40).all()
+
+
 # L_a = 512: whole query slabs, as rows past L_a hold zeros (0 * -inf); chunks of
 # 128 to 1024 video keys by the number of heads.  The bound of the other bf16
 # saliency tests.
