@@ -248,6 +248,7 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4_t;
 // than 2^8: the stale max keeps every probability below 256, exact after the
 // final division by the row sum taken against the same max.
 constexpr float kRescaleSlack = 8.0f;
+constexpr float kSlackWeight = 1.f / 256.f;  // 2^-kRescaleSlack
 
 template <bool B>
 struct CopyFlag {
@@ -1158,13 +1159,11 @@ sparse_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[dq][e] *= alpha;
     }
-    // only -inf scores so far: they weigh 0.  The slack is taken off the weights,
-    // which so stay at most 1 and keep P V within the range of V.
-    const float mref = m == -INFINITY ? 0.f : m + kRescaleSlack;
+    const float mref = m == -INFINITY ? 0.f : m;  // only -inf scores so far: they weigh 0
+    // the slack taken off exactly: weights of at most 1 keep P V within the range of V
     float p[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      p[e] = fast_exp2(log2_score(s[e], c, mref));
+    for (int e = 0; e < 4; ++e) p[e] = kSlackWeight * fast_exp2(log2_score(s[e], c, mref));
     if (x.key0 + kF32Keys > L) {  // rows past L weigh nothing, whatever row L-1 holds
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -1240,9 +1239,8 @@ sparse_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
     *reinterpret_cast<f32x4*>(o + (static_cast<size_t>(pair) * L + orow) * D + d4) = val;
     if (lse != nullptr && d4 == 0)
       lse[static_cast<size_t>(pair) * L + orow] =
-          den > 0.f ? static_cast<float>((static_cast<double>(M) + kRescaleSlack) *
-                                             0.6931471805599453 +
-                                         static_cast<double>(logf(den)))
+          den > 0.f ? static_cast<float>(static_cast<double>(M) * 0.6931471805599453 +
+                                         static_cast<double>(logf(den * (1.f / kSlackWeight))))
                 : -INFINITY;
   }
 }
