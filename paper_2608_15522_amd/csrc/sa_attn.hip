@@ -76,21 +76,36 @@ __host__ __device__ constexpr int xcd_first(int P, int x) {
 // (row, list entry) of every run's first entry; run c ends where run c + 1
 // starts, the last at row R, entry 0.  A row costs kRowCost entries besides its
 // own (list, Q rows, pipeline fill, epilogue: about 15 k cycles against 5.7 k
-// an entry of 128 keys), a run has at least kMinRun of them, and a cut within
-// kSnap entries of a list's end moves to that end.  starts[slots + 1].x says
-// whether the runs are to be used.  Whole rows claimed one at a time end with
-// the longest one, at 0.72 of an entry's usual time once it has the CU to
-// itself, or about a quarter of a row after the mean; runs are equal but
-// static, and end up to 10 % late on the slowest XCD, so they are used from
-// that line on.  At d 128, block 128, n_b 256, a quarter of the pairs kept and
-// 5 % of the rows full: 466 -> 209 us with one head (0.5 rows a slot), 647 ->
-// 473 with three, 717 -> 619 with four (max list / run 1.7), but 874 -> 907
-// with six (1.16) and 1106 -> 1202 with eight, where whole rows stay.
+// an entry of 128 keys at d 128), a run has at least kMinRun of them, and a cut
+// within kSnap entries of a list's end moves to that end.  starts[slots + 1].x says
+// whether the runs are to be used (RunRule).
 constexpr int kRowCost = 2;
 constexpr int kMinRun = 16;
 constexpr int kSnap = 4;
+// When runs are used, in list entries: claimed whole rows end with the longest one,
+// which has its CU to itself by then (`alone` of an entry's usual time; 0.6 if no two
+// rows share a CU at all), or, with more rows than slots, when the last round ends,
+// of which `tail` of the empty part counts; runs end together, after `ratio` of their
+// length (static, they wait for the slowest XCD) and the merge of what they share.
+// Fitted for each form over 1200 to 1800 calls that may cut their lists (1 to 32
+// pairs, 64 to 780 blocks, densities of 0.1 to 0.5, up to 10 % full rows), every one
+// timed with runs and with whole rows: a call then takes 0.84, 0.80, 0.75 and 0.75 of
+// the time of whole rows, heaviest first, on average (in the order below), 1.03, 1.03,
+// 1.00 and 1.02 of it at the 95th percentile.  One rule for all forms, from figures at
+// d 128 and block 128 alone, put one call in twenty to 1.08 times that time or more
+// and one in a hundred to 1.4 times.
+struct RunRule {
+  float alone, tail, ratio, merge;
+};
+template <int D, int BLOCK>
+constexpr RunRule run_rule() {
+  if constexpr (D == 128 && BLOCK == 128) return {1.f, 0.8f, 1.1f, 24.f};
+  if constexpr (D == 128 && BLOCK == 64) return {0.78f, 0.4f, 1.2f, 8.f};
+  if constexpr (D == 64 && BLOCK == 128) return {1.f, 0.8f, 1.1f, 16.f};
+  return {1.f, 0.8f, 1.2f, 16.f};
+}
 __device__ void cut_rows(const int32_t* __restrict__ kv_cnt, int2* __restrict__ starts, int slots,
-                         int R, int n_b) {
+                         int R, int n_b, RunRule rule) {
   __shared__ int wave_tot[1024 / 64], wave_max[1024 / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int K = ceil_div(R, 1024);  // rows per thread
@@ -123,8 +138,11 @@ __device__ void cut_rows(const int32_t* __restrict__ kv_cnt, int2* __restrict__ 
   }
   const int run = max(ceil_div(total, slots), kMinRun);
   if (tid == 0) {
-    const float whole = fmaxf(0.72f * longest, static_cast<float>(run) + 0.25f * total / R);
-    starts[slots + 1] = make_int2(whole > 1.1f * run ? 1 : 0, 0);
+    float whole = (R <= kXcds * kCusPerXcd ? 0.6f : rule.alone) * longest;
+    if (R > slots)
+      whole = fmaxf(whole, run + rule.tail * (ceil_div(R, slots) - static_cast<float>(R) / slots) *
+                                     total / R);
+    starts[slots + 1] = make_int2(whole > rule.ratio * run + rule.merge ? 1 : 0, 0);
   }
   for (int r = r0; r < r1; ++r) {
     const int cnt = row_cnt(r);
@@ -140,10 +158,11 @@ __device__ void cut_rows(const int32_t* __restrict__ kv_cnt, int2* __restrict__ 
 
 __global__ void __launch_bounds__(1024)
 schedule_rows_kernel(const int32_t* __restrict__ kv_cnt, int32_t* __restrict__ sched,
-                     int* __restrict__ claim, int P, int n_b, int2* __restrict__ starts, int slots) {
+                     int* __restrict__ claim, int P, int n_b, int2* __restrict__ starts, int slots,
+                     RunRule rule) {
   __shared__ int full_before[kMaxPairs / kXcds + 2];  // full rows of the list's earlier pairs
   if (sched == nullptr || blockIdx.x == kXcds) {
-    cut_rows(kv_cnt, starts, slots, P * n_b, n_b);
+    cut_rows(kv_cnt, starts, slots, P * n_b, n_b, rule);
     return;
   }
   const int x = blockIdx.x, np = xcd_pairs(P, x), tid = threadIdx.x;
@@ -1266,7 +1285,7 @@ static void sparse_attention_bf16(const uint16_t* q, const uint16_t* k, const ui
     int2* starts = reinterpret_cast<int2*>(ws + lay.starts);
     float* part = reinterpret_cast<float*>(ws + lay.part);
     hipLaunchKernelGGL(schedule_rows_kernel, dim3(direct ? 1 : kXcds + 1), dim3(1024), 0, s, kv_cnt,
-                       sched, claim, P, n_b, starts, slots);
+                       sched, claim, P, n_b, starts, slots, run_rule<D, BLOCK>());
     hipLaunchKernelGGL((sparse_attn_bf16_kernel<D, BLOCK, Rows::kSplit>), dim3(slots),
                        dim3(2 * BLOCK), 0, s, q, k, v, o, lse, kv_idx, kv_cnt, sched, claim, P, L,
                        n_b, c, nullptr, 0, H, 1, part, L, starts);
@@ -1276,7 +1295,7 @@ static void sparse_attention_bf16(const uint16_t* q, const uint16_t* k, const ui
   }
   if (!direct)
     hipLaunchKernelGGL(schedule_rows_kernel, dim3(kXcds), dim3(1024), 0, s, kv_cnt, sched, claim, P,
-                       n_b, nullptr, 0);
+                       n_b, nullptr, 0, RunRule{});
   hipLaunchKernelGGL((sparse_attn_bf16_kernel<D, BLOCK, Rows::kList>),
                      dim3(direct ? rows : slots), dim3(2 * BLOCK), 0, s, q, k, v, o,
                      lse, kv_idx, kv_cnt, sched, claim, P, L, n_b, c, nullptr, 0, H, 1, nullptr, L,

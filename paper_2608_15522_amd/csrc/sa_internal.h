@@ -110,7 +110,7 @@ inline bool direct_rows(int P, int n_b, int d, int block) {
 // Whether the lists may be cut into one equal run per slot (the schedule kernel
 // decides, from the lists' lengths): with more than four rows a slot, or lists
 // of less than 64 blocks, whole rows were at least as fast at every density
-// down to 10 %, and the calls are spared the combine launch (about 2 us).
+// down to 10 %, and the calls are spared the cut and the merge's launch (4 to 6 us).
 constexpr int kSplitRounds = 4;
 inline bool split_rows(int P, int n_b, int d, int block) {
   return n_b >= 64 && static_cast<long long>(P) * n_b <= kSplitRounds * attn_slots(d, block);
