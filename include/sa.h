@@ -291,7 +291,8 @@ int sa_build_block_mask_pooled(const double* qbar, const double* kbar, int B,
  *              into equal runs and merge the partial rows (f32) in run order;
  *              the size has room for that.  A workspace below it but of at
  *              least 2 * (4 * B*H*n_b rounded up to 256) + 2048 bytes is
- *              accepted too, and every row is then computed in one piece.
+ *              accepted too, and every row is then computed in one piece
+ *              (fp32 calls never cut a list and use no more than that).
  */
 int sa_sparse_attention(const void* q, const void* k, const void* v, void* o,
                         float* lse, int B, int H, int L, int d, int dtype,

@@ -156,6 +156,17 @@ def _workspace(call, B, H, L_v, L_a, d, block, device, ws):
     return ws
 
 
+def sparse_attention_workspace(B: int, H: int, L: int, d: int, block: int, dtype) -> int:
+    """Workspace bytes that sa_sparse_attention makes use of.  The room for partial
+    rows that sa_workspace_size counts (it does not know the dtype) is for bf16
+    calls; fp32 calls use the least size that the entry point accepts."""
+    need = sa_workspace_size(SA_CALL_SPARSE_ATTENTION, B, H, L, 1, d, block)
+    if dtype == torch.float32:
+        n_b = -(-L // block)
+        need = min(need, 2 * -(-4 * B * H * n_b // 256) * 256 + 2048)
+    return need
+
+
 def sa_cross_scores(q_a, k_v, q_v, k_a, scale, block, *, sal_v_tok=None,
                     sal_v_blk=None, sal_a_tok=None, accumulate=False,
                     want_tok=True, ws=None):
@@ -246,7 +257,9 @@ def sa_sparse_attention(q, k, v, scale, block, kv_idx, kv_cnt, *, o=None,
         o = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty(B, H, L, dtype=torch.float32, device=dev)
-    ws = _workspace(SA_CALL_SPARSE_ATTENTION, B, H, L, 1, d, block, dev, ws)
+    if ws is None:
+        need = sparse_attention_workspace(B, H, L, d, block, q.dtype)
+        ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
     _check(lib().sa_sparse_attention(
         _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), B, H, L, d, _dtype_code(q),
         float(scale), block, _ptr(kv_idx), _ptr(kv_cnt), _ptr(ws), _nbytes(ws),

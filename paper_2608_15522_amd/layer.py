@@ -34,9 +34,9 @@ class LayerPlan:
         self.kv_cnt = e(B, H, n_b, dt=i32)
         self.o = e(B, H, L_v, d, dt=dtype)
         self.lse = e(B, H, L_v) if want_lse else None
-        ws = max(sa.sa_workspace_size(c, B, H, L_v, L_a, d, block)
-                 for c in (sa.SA_CALL_CROSS_SCORES, sa.SA_CALL_BUILD_BLOCK_MASK,
-                           sa.SA_CALL_SPARSE_ATTENTION))
+        ws = max(*(sa.sa_workspace_size(c, B, H, L_v, L_a, d, block)
+                   for c in (sa.SA_CALL_CROSS_SCORES, sa.SA_CALL_BUILD_BLOCK_MASK)),
+                 sa.sparse_attention_workspace(B, H, L_v, d, block, dtype))
         self.ws = e(max(ws, 1), dt=u8)
         n_pad = sa.sa_pool_columns(n_b)
         self.qbar = e(B, H, d, n_pad, dt=torch.float64) if with_audio else None

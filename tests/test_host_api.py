@@ -131,6 +131,27 @@ def test_cross_attention_workspace():
         assert sa.sa_workspace_size(sa.SA_CALL_CROSS_ATTENTION, *bad) == 0
 
 
+def test_fp32_attention_workspace():
+    """Partial rows are bf16 calls' only: an fp32 layer of few rows holds no room
+    for them (68 MB at d = 128), a bf16 one does."""
+    import torch
+    from paper_2608_15522_amd.binding import sparse_attention_workspace
+    from paper_2608_15522_amd.layer import LayerPlan
+    for B, H, L, d, block in [(1, 4, 4680, 128, 64), (1, 2, 9000, 64, 128), (2, 24, 75600, 128, 128)]:
+        n_b = -(-L // block)
+        least = 2 * -(-4 * B * H * n_b // 256) * 256 + 2048
+        full = sa.sa_workspace_size(sa.SA_CALL_SPARSE_ATTENTION, B, H, L, 1, d, block)
+        assert sparse_attention_workspace(B, H, L, d, block, torch.float32) == least
+        assert sparse_attention_workspace(B, H, L, d, block, torch.bfloat16) == full >= least
+    sizes = {}
+    for dtype in (torch.float32, torch.bfloat16):
+        plan = LayerPlan(1, 4, 4680, 128, 128, 64, 18, 3, 0.088, dtype=dtype, device="cpu")
+        sizes[dtype] = plan.ws.numel()
+    cross = sa.sa_workspace_size(sa.SA_CALL_CROSS_SCORES, 1, 4, 4680, 128, 128, 64)
+    mask = sa.sa_workspace_size(sa.SA_CALL_BUILD_BLOCK_MASK, 1, 4, 4680, 128, 128, 64)
+    assert sizes[torch.float32] == max(cross, mask) < 2**23 < sizes[torch.bfloat16]
+
+
 def test_token_attention_workspace_rejects():
     for bad in [(0, 1, 10, 1, 64, 0), (1, 1, 10, 11, 64, 0), (1, 1, 10, -1, 64, 0),
                 (1, 1, 10, 1, 96, 0)]:
