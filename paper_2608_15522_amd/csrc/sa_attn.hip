@@ -20,13 +20,13 @@
 // only when a lane's max grows by more than 2^8.  Keys past L are -inf, rows
 // past L are never written.
 //
-// Rows go through a launch schedule: each
-// XCD takes every 8th (batch, head) pair, first the full rows of all its pairs
-// (protected rows hold the full list), then the other rows one pair at a time,
-// so that a pair's K/V blocks are shared through one XCD's L2 and the long full
-// rows do not run alone at the end of the launch.  Small calls and short pairs go
-// out directly, one workgroup a row (direct_rows).  Calls of few rows may cut
-// the rows' lists into equal runs instead, and merge the rows that runs share.
+// Rows go through a launch schedule: each XCD takes every 8th (batch, head) pair,
+// first the full rows of all its pairs (protected rows hold the full list), then
+// the other rows one pair at a time, so that a pair's K/V blocks are shared through
+// one XCD's L2 and the long full rows do not run alone at the end of the launch.
+// Small calls and short pairs go out directly, one workgroup a row (direct_rows).
+// Calls of few rows may cut the rows' lists into equal runs instead, and merge the
+// rows that runs share.
 //
 // Gather form: dense rows gathered by index (protected tokens) or all rows
 // of a query tensor of another length (cross-modal attention), every key
@@ -149,7 +149,9 @@ __device__ void cut_rows(const int32_t* __restrict__ kv_cnt, int2* __restrict__ 
     // cuts c * run in [before, before + cnt + kRowCost)
     for (int c = ceil_div(before, run); c * run < before + cnt + kRowCost; ++c) {
       const int e = c * run - before - kRowCost;
-      starts[c] = e < kSnap ? make_int2(r, 0) : cnt - e < kSnap ? make_int2(r + 1, 0) : make_int2(r, e);
+      starts[c] = e < kSnap         ? make_int2(r, 0)
+                  : cnt - e < kSnap ? make_int2(r + 1, 0)
+                                    : make_int2(r, e);
     }
     before += cnt + kRowCost;
   }
@@ -979,7 +981,8 @@ row_combine_kernel(const float* __restrict__ part, const int2* __restrict__ star
   if (cut.y == 0 || (from.x == cut.x && from.y > 0)) return;  // no shared row begins in run c
   int n = 2;  // parts: run c's second partial, then the first ones of runs c + 1, ...
   while (c + n <= runs && starts[c + n].x == cut.x && starts[c + n].y > 0) ++n;
-  const float2* ml = reinterpret_cast<const float2*>(part + 2 * static_cast<size_t>(runs) * BLOCK * D);
+  const float2* ml =
+      reinterpret_cast<const float2*>(part + 2 * static_cast<size_t>(runs) * BLOCK * D);
   const int pair = cut.x / n_b, row0 = (cut.x - pair * n_b) * BLOCK;
   constexpr int TPR = D / 4;
 #pragma unroll 4
@@ -1031,10 +1034,12 @@ row_combine_kernel(const float* __restrict__ part, const int2* __restrict__ star
 //                 that one 16-byte load of V feeds four channel tiles.
 // Each wave copies its own K tiles through its own LDS buffers (RowTile16)
 // and loads V into registers, both one tile ahead, so the loop has no
-// barrier.  The row max is raised only when a score exceeds it by 2^8 (decided per wave), so the exchange of
-// the max between the four lanes of a query is rare.
-// At B1 H4 L4680 d128 (0.28 of the pairs kept) it takes 172 us, 83 TFLOP/s,
-// of which the full rows' 293 tiles a wave group are the longest chain; the
+// barrier.  The row max is raised only when a score exceeds it by 2^8 (decided per
+// wave), so the exchange of the max between the four lanes of a query is rare.
+// At B1 H4 L4680 d128 (0.28 of the pairs kept) it takes 172 us, 83 TFLOP/s, the
+// matrix cores busy 0.55 of it: few and uneven workgroups, the full rows' 293 tiles
+// the longest chain, and every workgroup streams K and V for its own 16 rows (16 KB
+// past L1 a tile, 18 bytes a cycle and CU); the
 // one-thread-per-row form before it took 16.4 ms, this one with K loaded
 // straight into the operand layout 192-264 us.
 constexpr int kF32Waves = 4;
@@ -1367,13 +1372,13 @@ void launch_gather_attention_bf16(const uint16_t* q, const uint16_t* k, const ui
   float* part = ns > 1 ? reinterpret_cast<float*>(ws) : nullptr;
   const dim3 grid(P * ceil_div(n_rows, kTokRowBlock) * ns);
   if (d == 128)
-    hipLaunchKernelGGL((sparse_attn_bf16_kernel<128, kTokRowBlock, Rows::kGather>), grid, dim3(256), 0,
-                       s, q, k, v, o, lse, nullptr, nullptr, nullptr, nullptr, P, Lk, n_b, c, rows,
-                       n_rows, H, ns, part, Lq, nullptr);
+    hipLaunchKernelGGL((sparse_attn_bf16_kernel<128, kTokRowBlock, Rows::kGather>), grid,
+                       dim3(256), 0, s, q, k, v, o, lse, nullptr, nullptr, nullptr, nullptr, P, Lk,
+                       n_b, c, rows, n_rows, H, ns, part, Lq, nullptr);
   else
-    hipLaunchKernelGGL((sparse_attn_bf16_kernel<64, kTokRowBlock, Rows::kGather>), grid, dim3(256), 0,
-                       s, q, k, v, o, lse, nullptr, nullptr, nullptr, nullptr, P, Lk, n_b, c, rows,
-                       n_rows, H, ns, part, Lq, nullptr);
+    hipLaunchKernelGGL((sparse_attn_bf16_kernel<64, kTokRowBlock, Rows::kGather>), grid,
+                       dim3(256), 0, s, q, k, v, o, lse, nullptr, nullptr, nullptr, nullptr, P, Lk,
+                       n_b, c, rows, n_rows, H, ns, part, Lq, nullptr);
   if (ns > 1) {
     const size_t threads = static_cast<size_t>(P) * n_rows * (d / 4);
     const dim3 cgrid(static_cast<unsigned>((threads + 255) / 256));

@@ -219,9 +219,10 @@ __device__ __forceinline__ void stream_keys(const KeyRing<D>& ring, const char* 
 // Lane-local online log2-sum-exp over the keys of KEYS_A units, for the two
 // query columns of the lane.  The running max m starts at the max of unit 0
 // (the lowest finite value at least: against it units whose scores are all
-// -inf, wherever a chunk begins, weigh 0 instead of -inf - -inf) and is raised only when a unit's sum against it reaches kSumGuard, so the
-// per-score work is one FMA, one exp2 and one add.  Keys >= key_end (tail of
-// the last tile) are masked to -inf.
+// -inf, wherever a chunk begins, weigh 0 instead of -inf - -inf) and is raised
+// only when a unit's sum against it reaches kSumGuard, so the per-score work is
+// one FMA, one exp2 and one add.  Keys >= key_end (tail of the last tile) are
+// masked to -inf.
 template <int D>
 struct LseAcc {
   static constexpr int VPS = 32 / (D / 8);  // scores per lane per slot
@@ -845,8 +846,8 @@ void launch_finalize(const float* colmass, float* sal_v_tok, float* sal_v_blk, i
   hipLaunchKernelGGL(saliency_finalize_kernel, wide_grid(static_cast<long>(n_v) + n_a, B),
                      dim3(kFinThreads), 0, s, colmass, sal_v_tok, sal_v_blk, H, L_v, block,
                      1.0f / (static_cast<float>(H) * static_cast<float>(L_a)), v2a_part, sal_a_tok,
-                     H * nchunk3, L_a, n_a, 1.0f / (static_cast<float>(H) * static_cast<float>(L_v)),
-                     accumulate);
+                     H * nchunk3, L_a, n_a,
+                     1.0f / (static_cast<float>(H) * static_cast<float>(L_v)), accumulate);
 }
 
 // ---- fp32 path --------------------------------------------------------------
@@ -1056,7 +1057,8 @@ row_lse2_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
 // streams the chunk, kF32XLse queries at a time, whose LSEs are merged into
 // LDS first; the 4 lanes of a key are added at the end.
 template <int D, int SPLIT>
-__global__ void __launch_bounds__(64 * kF32XWaves * SPLIT) __attribute__((amdgpu_waves_per_eu(SPLIT > 1 ? 4 : 5)))
+__global__ void __launch_bounds__(64 * kF32XWaves * SPLIT)
+    __attribute__((amdgpu_waves_per_eu(SPLIT > 1 ? 4 : 5)))
 colmass_f32_kernel(F32Dir a, F32Dir v, Log2Scale c) {
   constexpr int kRingBytes = RowRing16<D>::kStages * RowRing16<D>::kBytes;
   __shared__ __attribute__((aligned(1024))) char ring_lds[SPLIT * kRingBytes];
@@ -1209,7 +1211,8 @@ void cross_bf16(const uint16_t* q_a, const uint16_t* k_v, const uint16_t* q_v,
   float2* lse_part = reinterpret_cast<float2*>(ws + lay.lse_part);
   float* lse_a = reinterpret_cast<float*>(ws + lay.v2a_head);
   const size_t nlse = static_cast<size_t>(P) * L_a;
-  const long max_chunks = static_cast<long>((lay.v2a_head - lay.lse_part) / (sizeof(float2) * nlse));
+  const long max_chunks =
+      static_cast<long>((lay.v2a_head - lay.lse_part) / (sizeof(float2) * nlse));
   const int ck = key_chunk(L_v, static_cast<long>(nslab) * P, max_chunks);
   const int nchunk = ceil_div(L_v, ck);
   hipLaunchKernelGGL(a2v_lse_partial_kernel<D>, dim3(nchunk, nslab, P), dim3(kXNT), 0, s,
@@ -1252,17 +1255,20 @@ void cross_f32(const float* q_a, const float* k_v, const float* q_v,
   float* lse_v = take(n_v);
   float* v2a_part = take(n_a * nchunk3);
   float* lse_a = take(0);
-  // Video keys per a->v log-sum-exp workgroup: 1024, or down to 256 while the
+  // Video keys per a->v log-sum-exp workgroup: kLseChunk (a sixteenth of longer
+  // clips), whose partials the workspace has room for, or down to 256 while the
   // launch has less than two workgroups a CU and the rest of the workspace holds
   // the partials, which the column-mass workgroups merge where they read them
   // (11.3 -> 5.5 us at B1 H2 L_v1024 L_a128 d64; at H8 L_v4680 L_a512 d128
   // chunks of 400 keys were 10 us slower than 1024).
   const bool rev = q_v != nullptr;
-  const long room = static_cast<long>((cross_ws_layout(B, H, L_v, L_a).total - off) / (sizeof(float) * n_a));
+  const long room =
+      static_cast<long>((cross_ws_layout(B, H, L_v, L_a).total - off) / (sizeof(float) * n_a));
   auto lse_wgs = [&](int chunk) {
-    return static_cast<long>(P) * (ceil_div(L_a, 16) * ceil_div(L_v, chunk) + (rev ? ceil_div(L_v, 16) : 0));
+    return static_cast<long>(P) * (static_cast<long>(ceil_div(L_a, 16)) * ceil_div(L_v, chunk) +
+                                   (rev ? ceil_div(L_v, 16) : 0));
   };
-  int lse_chunk = std::max(1024, ceil_div(ceil_div(L_v, kF32XMerge), 16) * 16);
+  int lse_chunk = std::max(kLseChunk, ceil_div(ceil_div(L_v, kF32XMerge), 16) * 16);
   while (lse_chunk > 256 && lse_wgs(lse_chunk) < 2 * kXcds * kCusPerXcd &&
          ceil_div(L_v, lse_chunk / 2) <= std::min(room, static_cast<long>(kF32XMerge)))
     lse_chunk /= 2;

@@ -11,7 +11,8 @@ namespace sa {
 
 // Tunables fixed at build time.
 constexpr int kLseChunk = 1024;   // video keys per a->v log-sum-exp partial that the
-                                  // workspace holds room for (fp32 path: the chunk)
+                                  // workspace holds room for (fp32: the chunk of long
+                                  // clips, shortened where room and size allow)
 constexpr int kMaxKeyChunk = 1024;  // most video keys of an a->v workgroup, bf16 path
 constexpr int kQSlab = 512;       // queries per 16-wave workgroup slab
 constexpr int kV2aChunk = 512;    // video queries per v->a workgroup
