@@ -299,7 +299,10 @@ __device__ __forceinline__ float max_halves(float x) {
 // runs the part of the list that it holds goes to partial 2c (the run starts
 // inside the list) or 2c + 1 (it starts at the list's start) for
 // row_combine_kernel.
-enum class Rows { kList, kGather, kSplit };
+// LIST: persistent workgroups claim whole rows by `sched`, or, without one, one
+// workgroup a row in index order; DIRECT: one workgroup a row, full rows first (a
+// form of its own: in the persistent one its code costs 0.5 to 0.9 %).
+enum class Rows { kList, kDirect, kGather, kSplit };
 template <int D, int BLOCK, Rows ROWS>
 __global__ void __launch_bounds__(BLOCK * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
 sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
@@ -314,6 +317,7 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
                         const int2* __restrict__ starts) {
   constexpr bool GATHER = ROWS == Rows::kGather;
   constexpr bool SPLIT = ROWS == Rows::kSplit;
+  constexpr bool DIRECT = ROWS == Rows::kDirect;
   constexpr int NW = BLOCK / 32;             // waves per workgroup
   constexpr int TPB = BLOCK / kTile;         // tiles per key block
   constexpr int KC = D / 16;                 // k-steps of Q K^T
@@ -341,12 +345,10 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
   // evens out XCDs that run at different speeds or own fewer pairs (an XCD
   // without a pair of its own starts at list x % P).  Each row is computed the
   // same way whichever workgroup takes it.  Otherwise there is one workgroup
-  // per row: full rows of every pair first (direct_rows; one more dependent load,
-  // against the claim and the list of a persistent workgroup), or, for dense rows,
-  // XCD-major over pairs.
+  // per row (dense rows: XCD-major over pairs).
   const bool runs =
       SPLIT && __builtin_amdgcn_readfirstlane(starts[static_cast<int>(gridDim.x) + 1].x) != 0;
-  const bool persistent = !GATHER && !runs && sched != nullptr;
+  const bool persistent = !GATHER && !DIRECT && !runs && sched != nullptr;
   const int xcd = P < kXcds ? (blockIdx.x & 7) % P : blockIdx.x & 7;
   int exhausted = 0;                   // lists found empty (thread 0)
   // SPLIT: consecutive runs on one XCD, so that a pair's K/V blocks are shared
@@ -399,12 +401,11 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
       pair = blockIdx.x % P;
       rank = blockIdx.x / P;
       if (SPLIT && rank >= n_b) break;  // one workgroup per slot, fewer rows
-      if constexpr (!GATHER) {
+      if constexpr (DIRECT || SPLIT) {
         // in index order two full rows may share a CU, or start last (1.2 times as
         // long); at most one row a CU, the order is the same to all
-        r = P * n_b > kXcds * kCusPerXcd
-                ? full_first_row(kv_cnt + static_cast<size_t>(pair) * n_b, n_b, rank)
-                : rank;
+        if (DIRECT || P * n_b > kXcds * kCusPerXcd)
+          rank = full_first_row(kv_cnt + static_cast<size_t>(pair) * n_b, n_b, rank);
       }
     }
   }
@@ -419,6 +420,7 @@ sparse_attn_bf16_kernel(const uint16_t* __restrict__ q,
     kb0 = n_b * split / n_split;
     cnt = n_b * (split + 1) / n_split - kb0;
   } else {
+    if (!persistent && !runs) r = rank;
     cnt = kv_cnt[row_base + r];
     cnt = cnt < 0 ? 0 : (cnt > n_b ? n_b : cnt);
     idx = kv_idx + (row_base + r) * n_b;
@@ -1298,13 +1300,18 @@ static void sparse_attention_bf16(const uint16_t* q, const uint16_t* k, const ui
                        part, starts, n_b, L, o, lse);
     return;
   }
+  if (direct && rows > kXcds * kCusPerXcd) {
+    hipLaunchKernelGGL((sparse_attn_bf16_kernel<D, BLOCK, Rows::kDirect>), dim3(rows),
+                       dim3(2 * BLOCK), 0, s, q, k, v, o, lse, kv_idx, kv_cnt, nullptr, nullptr, P,
+                       L, n_b, c, nullptr, 0, H, 1, nullptr, L, nullptr);
+    return;
+  }
   if (!direct)
     hipLaunchKernelGGL(schedule_rows_kernel, dim3(kXcds), dim3(1024), 0, s, kv_cnt, sched, claim, P,
                        n_b, nullptr, 0, RunRule{});
-  hipLaunchKernelGGL((sparse_attn_bf16_kernel<D, BLOCK, Rows::kList>),
-                     dim3(direct ? rows : slots), dim3(2 * BLOCK), 0, s, q, k, v, o,
-                     lse, kv_idx, kv_cnt, sched, claim, P, L, n_b, c, nullptr, 0, H, 1, nullptr, L,
-                     nullptr);
+  hipLaunchKernelGGL((sparse_attn_bf16_kernel<D, BLOCK, Rows::kList>), dim3(direct ? rows : slots),
+                     dim3(2 * BLOCK), 0, s, q, k, v, o, lse, kv_idx, kv_cnt, sched, claim, P, L,
+                     n_b, c, nullptr, 0, H, 1, nullptr, L, nullptr);
 }
 
 static void sparse_attention_bf16(const uint16_t* q, const uint16_t* k, const uint16_t* v,
