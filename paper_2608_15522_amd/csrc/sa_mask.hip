@@ -484,10 +484,12 @@ static void launch_pool(const T* q, const T* k, double* qbar, double* kbar, int 
                         hipStream_t s) {
   const int n_b = ceil_div(L, block);
   const int n_pad = mask_n_pad(n_b);
-  // 8 blocks a workgroup write the means as 64-byte runs and win once the
-  // chip is full (three workgroups a CU); below that fewer blocks each spread
-  // the reads over more CUs.
-  constexpr long kFull = 3 * 256;
+  // 8 blocks a workgroup write the means as 64-byte runs and win once one and a half
+  // workgroups a CU have some; below that fewer blocks each spread the reads over more
+  // CUs.  Over 6800 calls (both types, head and block sizes, 60 to 9000 blocks) this
+  // line leaves 0.6 % to the best of the four on average; at three workgroups a CU
+  // 1.7 %, and calls of 3000 to 6000 blocks 6 to 9 % slower than 8 blocks always.
+  constexpr long kFull = 384;
 #define SA_POOL(PB)                                                                            \
   hipLaunchKernelGGL((block_pool_kernel<T, D, PB>), dim3(ceil_div(n_b, PB), P), dim3(256), 0, \
                      s, q, k, qbar, kbar, L, block, n_b, n_pad)

@@ -46,8 +46,9 @@ def test_block_ranking_of_many_items(B, n_b):
     assert torch.equal(flag, ref)
 
 
-# 1, 2, 4 and 8 blocks per pooling workgroup (768 workgroups are wanted)
-@pytest.mark.parametrize("H,n_b,tail,dtype", [(24, 7, 5, torch.bfloat16), (64, 24, 64, torch.bfloat16),
+# 1, 2, 4 and 8 blocks per pooling workgroup (384 workgroups are wanted)
+@pytest.mark.parametrize("H,n_b,tail,dtype", [(24, 7, 5, torch.bfloat16), (64, 12, 9, torch.bfloat16),
+                                              (64, 24, 64, torch.bfloat16),
                                               (64, 47, 1, torch.float32), (64, 97, 33, torch.bfloat16)])
 def test_pooled_scores(H, n_b, tail, dtype):
     d, block = 64, 64
