@@ -308,7 +308,7 @@ int sa_sparse_attention(const void* q, const void* k, const void* v, void* o,
  *
  * Arguments, results and errors are those of sa_sparse_attention; the same
  * kernels run, so the outputs are bitwise those of sa_sparse_attention with a
- * workspace of sa_workspace_size bytes.  The scratch lives in a 70 MiB array
+ * workspace of sa_workspace_size bytes.  The scratch lives in a 69 MiB array
  * that the library holds on each device it runs on until the process ends.
  * 4 MiB of it bound the size of a call (the launch order and schedule of the
  * query blocks, two arrays of B*H*n_b int32, and 8 row counters):

@@ -13,7 +13,7 @@
 //    per-wave totals write the kept tokens in ascending order.
 //    Bound by latency: one workgroup, a chain of barriers.  Two bits a step
 //    (counts by wave sums, candidates copied to LDS) took 53 us at L =
-//    32760, 17 at 2049 and 10 at 512 against 26, 8 and 8.
+//    32760, 17 at 2049 and 10 at 512 against 27, 8 and 8.
 // The dense attention rows of the protected tokens are the gather variant of
 // the attention kernel (sa_attn.hip).
 #include "sa_device.h"
